@@ -248,10 +248,12 @@ typedef struct {
                              or the given workspace in the solvers                  */
     double tol;           /* stop when |beta_j s_j| <= tol * max(|theta|, 1) (1e-10) */
     int32_t reorth;       /* Gram-Schmidt per step (default 2): 0 = three-term only, 1 = one
-                             full pass, 2 = two full passes (CGS2), 3 = the two projections
-                             of CGS2 from one read of the basis, the second one's
-                             coefficients through the Gram matrix of the stored vectors
-                             (ground state; with locked vectors it falls back to 2)    */
+                             full pass, 2 = two passes, the first on the two vectors the
+                             Lanczos recurrence couples H S_j to (S_{j-1}, S_j), the second
+                             on every stored and locked vector, 3 = two full projections
+                             from one read of the basis, the second one's coefficients
+                             through the Gram matrix of the stored vectors (ground state;
+                             with locked vectors it falls back to 2)                     */
     int32_t check_every;  /* steps between convergence tests (default 4)            */
     int32_t refine;       /* 1: report the FP64 Rayleigh quotient of the Ritz vector */
     int32_t keep;         /* restart: 0 = from the current Ritz vector alone (default);

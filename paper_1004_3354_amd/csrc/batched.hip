@@ -456,7 +456,7 @@ __global__ __launch_bounds__(256) void kb_tridiag(BState st, BDims dm, double to
     }
     __syncthreads();
     double *out = st.tri + (int64_t)s * dm.mt;
-    k_tridiag_lowest_body(alpha, beta, m, out, nullptr);
+    k_tridiag_lowest_body(alpha, beta, m, out);
     if (threadIdx.x == 0) {  // the body's result is complete in thread 0
         const double theta = out[0], res = out[1], bl = out[2];
         const double scale = fmax(fabs(theta), 1.0);
@@ -605,7 +605,7 @@ __global__ __launch_bounds__(256) void kb_restart_fin(BState st, BDims dm) {
         return;
     }
     if (brk_s) {  // finish on the kept block
-        k_tridiag_lowest_body(alpha, beta, k, st.tri + (int64_t)s * dm.mt, nullptr);
+        k_tridiag_lowest_body(alpha, beta, k, st.tri + (int64_t)s * dm.mt);
         if (threadIdx.x == 0) {
             st.theta[s] = st.tri[(int64_t)s * dm.mt];
             st.resid[s] = 0.0;

@@ -7,9 +7,18 @@
 // handle's precision and sigma_i an FP64 scale, so a new vector is never
 // rescaled in memory.  One step j:
 //   Y = H S_j                                  (matrix-free apply)
-//   a_i = <S_i, Y> over locked vectors and S_0..S_j, gamma_i = sigma_i^2 a_i
-//   Y <- Y - sum_i gamma_i S_i                 (classical Gram-Schmidt)
-//   repeated once more ("twice is enough"), alpha_j = sum of the two gamma_j
+//   W = Y - a S_j - b S_{j-1},  a = sigma_j^2 <S_j, Y>, b = sigma_{j-1}^2 <S_{j-1}, Y>
+//   gamma_i = sigma_i^2 <S_i, W> over locked vectors and S_0..S_j
+//   Y <- W - sum_i gamma_i S_i                 (classical Gram-Schmidt)
+// with alpha_j = a + gamma_j: Gram-Schmidt twice ("twice is enough"), the first
+// time on the two vectors on which H S_j has a component by the Lanczos
+// recurrence, the second time on all of them.  Every other component of Y is at
+// the level of rounding (of the locked vectors' residuals) already before the
+// first projection, which is what a first pass over all vectors would leave,
+// so the second pass ends at the same orthogonality (FP64 1e-15, FP32 1e-8,
+// with explicit and implicit restarts and locked vectors alike) while the
+// stored vectors are read twice per step instead of four times.  W is formed
+// on the fly in FP64 and never stored.
 // reorth = 3 gives the same two projections with one read of the basis per
 // step: the second pass's dots are a_i - sum_k G_ik gamma_k with G_ik =
 // <S_i, S_k> (exact for the update Y - sum gamma_k S_k), and the new row of G
@@ -33,11 +42,18 @@ static constexpr int kMaxVec = 1024;  // locked + stored basis vectors per kerne
 static constexpr int kIRMaxIn = 257;  // implicit restart: at most 256 basis vectors + the residual
 static constexpr int kIRMaxOut = 17;  // and at most 16 kept vectors + the new residual
 
-int reduce_blocks(int64_t n) {
-    int64_t b = (n + 4095) / 4096;
-    if (b < 1) b = 1;
-    if (b > 2048) b = 2048;
-    return (int)b;
+// Workgroups (= partial sums per vector) of the dot kernels: 1024 elements each
+// (one group of four per thread), at most 2048 workgroups.
+int reduce_blocks(int64_t n) { return (int)std::min<int64_t>(std::max<int64_t>((n + 1023) / 1024, 1), 2048); }
+
+// The update kernel splits the vectors of a sum over a workgroup's four waves
+// for n up to this (256 elements per workgroup): at D = 4900 with 36 vectors
+// 10 us -> 3 us.  Beyond it one wave takes all vectors of its elements, 1024
+// elements per workgroup, and there are workgroups enough.
+static constexpr int64_t kSplitMax = 131072;
+static int update_blocks(int64_t n) {
+    const int64_t per = n <= kSplitMax ? 256 : 1024;
+    return (int)std::min<int64_t>(std::max<int64_t>((n + per - 1) / per, 1), 2048);
 }
 
 // contiguous element range of block `blk` out of `nblk`
@@ -48,6 +64,29 @@ __device__ __forceinline__ void block_range(int64_t n, int nblk, int blk, int64_
     b = a + chunk;
     if (a > n) a = n;
     if (b > n) b = n;
+}
+
+// Sums over a wave of G values per lane (G a power of two, at most 64): lane l
+// returns the total of value l >> (6 - log2 G).  Each exchange halves the
+// values a lane still carries, so G sums cost G + 5 - log2 G exchanges instead
+// of 6 G.
+template <int G>
+__device__ __forceinline__ double wave_sums(double (&v)[G]) {
+    const int lane = (int)threadIdx.x & 63;
+    int m = 32;
+#pragma unroll
+    for (int h = G / 2; h >= 1; h /= 2) {
+        const bool up = (lane & m) != 0;
+#pragma unroll
+        for (int i = 0; i < h; ++i) {
+            const double keep = up ? v[i + h] : v[i], send = up ? v[i] : v[i + h];
+            v[i] = keep + __shfl_xor(send, m, 64);
+        }
+        m >>= 1;
+    }
+    double r = v[0];
+    for (; m >= 1; m >>= 1) r += __shfl_xor(r, m, 64);
+    return r;
 }
 
 template <int BS>
@@ -64,113 +103,11 @@ __device__ __forceinline__ double block_sum_any(double v, double *red) {
     return s;
 }
 
-// partials[v * nblk + blk] = sum over the block's range of S_v[n] * Y[n]
-template <typename TX, int G>
-__global__ __launch_bounds__(kRedBS) void k_multidot(const TX *const *vecs, int nvec, const TX *y, int64_t n,
-                                                     double *partials) {
-    __shared__ double red[kRedBS / 64];
-    const int nblk = gridDim.x, blk = blockIdx.x;
-    int64_t a, b;
-    block_range(n, nblk, blk, a, b);
-    for (int g0 = 0; g0 < nvec; g0 += G) {
-        double acc[G];
-#pragma unroll
-        for (int i = 0; i < G; ++i) acc[i] = 0.0;
-        const TX *vp[G];
-#pragma unroll
-        for (int i = 0; i < G; ++i) vp[i] = vecs[(g0 + i < nvec) ? g0 + i : g0];
-        for (int64_t k = a + threadIdx.x; k < b; k += kRedBS) {
-            const double yv = (double)y[k];
-#pragma unroll
-            for (int i = 0; i < G; ++i)
-                if (g0 + i < nvec) acc[i] += (double)vp[i][k] * yv;
-        }
-#pragma unroll
-        for (int i = 0; i < G; ++i) {
-            if (g0 + i >= nvec) break;
-            const double s = block_sum_any<kRedBS>(acc[i], red);
-            if (threadIdx.x == 0) partials[(int64_t)(g0 + i) * nblk + blk] = s;
-        }
-    }
-}
-
-// Two right-hand sides in one read of the basis:
-// partials[v * nblk + blk] = sum S_v Y, partials[(nvec + v) * nblk + blk] = sum S_v Z
-template <typename TX, int G>
-__global__ __launch_bounds__(kRedBS) void k_multidot2(const TX *const *vecs, int nvec, const TX *y, const TX *z,
-                                                      int64_t n, double *partials) {
-    __shared__ double red[kRedBS / 64];
-    const int nblk = gridDim.x, blk = blockIdx.x;
-    int64_t a, b;
-    block_range(n, nblk, blk, a, b);
-    for (int g0 = 0; g0 < nvec; g0 += G) {
-        double ay[G], az[G];
-#pragma unroll
-        for (int i = 0; i < G; ++i) ay[i] = az[i] = 0.0;
-        const TX *vp[G];
-#pragma unroll
-        for (int i = 0; i < G; ++i) vp[i] = vecs[(g0 + i < nvec) ? g0 + i : g0];
-        for (int64_t k = a + threadIdx.x; k < b; k += kRedBS) {
-            const double yv = (double)y[k], zv = (double)z[k];
-#pragma unroll
-            for (int i = 0; i < G; ++i)
-                if (g0 + i < nvec) {
-                    const double sv = (double)vp[i][k];
-                    ay[i] += sv * yv;
-                    az[i] += sv * zv;
-                }
-        }
-#pragma unroll
-        for (int i = 0; i < G; ++i) {
-            if (g0 + i >= nvec) break;
-            const double sy = block_sum_any<kRedBS>(ay[i], red);
-            const double sz = block_sum_any<kRedBS>(az[i], red);
-            if (threadIdx.x == 0) {
-                partials[(int64_t)(g0 + i) * nblk + blk] = sy;
-                partials[(int64_t)(nvec + g0 + i) * nblk + blk] = sz;
-            }
-        }
-    }
-}
-
-// Y[n] = post * ((assign ? 0 : Y[n]) - sum_i coef[i] S_i[n]) with post =
-// sqrt(*post_sig2) (1 if NULL); optional norm partials of the stored result.
-template <typename TX>
-__global__ __launch_bounds__(kRedBS) void k_lincomb(const TX *const *vecs, const double *coef, int nvec, TX *y,
-                                                    int64_t n, int assign, double sign, double *norm_part,
-                                                    const double *post_sig2) {
-    __shared__ double c[kMaxVec];
-    __shared__ const TX *p[kMaxVec];
-    __shared__ double red[kRedBS / 64];
-    for (int i = threadIdx.x; i < nvec; i += kRedBS) {
-        c[i] = sign * coef[i];
-        p[i] = vecs[i];
-    }
-    __syncthreads();
-    int64_t a, b;
-    block_range(n, gridDim.x, blockIdx.x, a, b);
-    const double post = post_sig2 ? sqrt(*post_sig2) : 1.0;
-    double nrm = 0.0;
-    for (int64_t k = a + threadIdx.x; k < b; k += kRedBS) {
-        double v = assign ? 0.0 : (double)y[k];
-        for (int i = 0; i < nvec; ++i) v -= c[i] * (double)p[i][k];
-        const TX st = (TX)(post * v);
-        y[k] = st;
-        nrm += (double)st * (double)st;
-    }
-    if (norm_part) {
-        const double s = block_sum_any<kRedBS>(nrm, red);
-        if (threadIdx.x == 0) norm_part[blockIdx.x] = s;
-    }
-}
-
-// Vector forms of the three kernels above for the single-sector solver: each
-// thread takes four consecutive elements per iteration (one 16-byte load per
-// FP32 vector, two per FP64 vector) and keeps G vectors' loads in flight.
-// Block ranges start at multiples of 64 elements and slots are 256-byte
-// aligned, so every group of four inside a block is aligned; a block's ragged
-// end is done element by element.  Same partial layout and fixed reduction
-// order per block as the scalar forms.
+// The vector kernels: each thread takes four consecutive elements per iteration
+// (one 16-byte load per FP32 vector, two per FP64 vector) and keeps several
+// vectors' loads in flight.  Block ranges start at multiples of 64 elements and
+// slots are 256-byte aligned, so every group of four inside a block is aligned;
+// a block's ragged end is done element by element.  Fixed reduction order.
 // (vectors declared with element alignment only: a locked vector inside a
 // caller's [k][D] array starts at a multiple of D elements, and gfx950 global
 // memory accepts 16-byte accesses at element alignment)
@@ -206,120 +143,367 @@ __device__ __forceinline__ void store4(TX *p, const Q4<TX> &q) {
     }
 }
 
-// partials[v * nblk + blk] = sum S_v Y (and with Z, when z != NULL, at
-// partials[(nvec + v) * nblk + blk])
+// Fixed-order sum of p[0..n), n <= 8 * 256, by one workgroup of 256: thread
+// t adds p[t], p[t + 256], ... in that order (all its loads issued at once),
+// then a pairwise tree over the threads, strides 128, 64 (through LDS, each wave
+// for itself) and 32 .. 1 (inside the wave).  sh: 256 doubles.  The result is
+// valid in every thread.
+__device__ __forceinline__ double wg_sum_fixed(const double *p, int n, double *sh) {
+    double v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+        const int i = (int)threadIdx.x + 256 * q;
+        v[q] = i < n ? p[i] : 0.0;
+    }
+    double s = 0.0;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s += v[q];
+    sh[threadIdx.x] = s;
+    __syncthreads();
+    const int l = (int)threadIdx.x & 63;
+    s = (sh[l] + sh[l + 128]) + (sh[l + 64] + sh[l + 192]);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
+    __syncthreads();
+    return s;
+}
+
+// The norm of the vector the previous update stored, left as partial sums:
+// n2 = ||w''||^2 -> *beta = sqrt(n2), *sig2 = 1/n2 (0 on exact breakdown).
+// One workgroup of the next kernel that needs nothing of it does this, so it
+// costs no launch of its own.
+struct NormJob {
+    const double *part = nullptr;
+    int n = 0;
+    double *sig2 = nullptr, *beta = nullptr;
+};
+__device__ __forceinline__ void norm_job(const NormJob &nj, double *sh) {
+    const double n2 = wg_sum_fixed(nj.part, nj.n, sh);
+    if (threadIdx.x == 0) {
+        *nj.beta = sqrt(n2);
+        *nj.sig2 = n2 > 0.0 ? 1.0 / n2 : 0.0;
+    }
+}
+
+// First projection of a step, on the last nloc (1 or 2) vectors of the table:
+// part = the partial sums of their dots with Y (rows in table order), sig2 of
+// the whole table; loc[0] = a (S_j), loc[1] = b (S_{j-1}) are left for the update.
+struct LocalPass {
+    const double *part = nullptr, *sig2 = nullptr;
+    int nloc = 0;
+    double *loc = nullptr;
+};
+
+// One group of dots over the elements [a, b): vectors vecs[g0 .. g0 + cnt), cnt <=
+// G (G a multiple of 4, the unused ones repeat the group's first vector and are
+// not written), all G loads in flight.
 template <typename TX, int G, bool TWO>
-__global__ __launch_bounds__(kRedBS) void k_multidot_v4(const TX *const *vecs, int nvec, const TX *y, const TX *z,
-                                                        int64_t n, double *partials) {
-    __shared__ double red[kRedBS / 64];
-    const int nblk = gridDim.x, blk = blockIdx.x;
-    int64_t a, b;
-    block_range(n, nblk, blk, a, b);
-    for (int g0 = 0; g0 < nvec; g0 += G) {
-        double ay[G], az[G];
+__device__ __forceinline__ void dots_group(const TX *const *vecs, int g0, int cnt, int nvec, const TX *y, const TX *z,
+                                           int64_t a, int64_t b, double *partials, int nblk, int blk,
+                                           double (*red)[kRedBS / 64][16]) {
+    constexpr int GP = G <= 2 ? 2 : (G <= 4 ? 4 : (G <= 8 ? 8 : 16));  // power of two for the reduction
+    double ay[GP], az[GP];
 #pragma unroll
-        for (int i = 0; i < G; ++i) ay[i] = az[i] = 0.0;
-        const TX *vp[G];
+    for (int i = 0; i < GP; ++i) ay[i] = az[i] = 0.0;
+    const TX *vp[G];
 #pragma unroll
-        for (int i = 0; i < G; ++i) vp[i] = vecs[(g0 + i < nvec) ? g0 + i : g0];
-        int64_t k = a + 4 * (int64_t)threadIdx.x;
-        for (; k + 4 <= b; k += 4 * kRedBS) {
-            const Q4<TX> yv = load4(y + k);
-            Q4<TX> zv;
-            if constexpr (TWO) zv = load4(z + k);
-            Q4<TX> sv[G];
+    for (int i = 0; i < G; ++i) vp[i] = vecs[g0 + (i < cnt ? i : 0)];
+    int64_t k = a + 4 * (int64_t)threadIdx.x;
+    for (; k + 4 <= b; k += 4 * kRedBS) {
+        const Q4<TX> yv = load4(y + k);
+        Q4<TX> zv;
+        if constexpr (TWO) zv = load4(z + k);
+        Q4<TX> sv[G];
 #pragma unroll
-            for (int i = 0; i < G; ++i)
-                if (g0 + i < nvec) sv[i] = load4(vp[i] + k);
+        for (int i = 0; i < G; ++i) sv[i] = load4(vp[i] + k);
 #pragma unroll
-            for (int i = 0; i < G; ++i) {
-                if (g0 + i >= nvec) break;
+        for (int i = 0; i < G; ++i)
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    ay[i] += (double)sv[i].v[e] * (double)yv.v[e];
-                    if constexpr (TWO) az[i] += (double)sv[i].v[e] * (double)zv.v[e];
-                }
+            for (int e = 0; e < 4; ++e) {
+                ay[i] += (double)sv[i].v[e] * (double)yv.v[e];
+                if constexpr (TWO) az[i] += (double)sv[i].v[e] * (double)zv.v[e];
             }
-        }
-        for (int64_t e = k; e < b && e < k + 4; ++e) {  // ragged end of the block
-#pragma unroll
-            for (int i = 0; i < G; ++i) {
-                if (g0 + i >= nvec) break;
-                ay[i] += (double)vp[i][e] * (double)y[e];
-                if constexpr (TWO) az[i] += (double)vp[i][e] * (double)z[e];
-            }
-        }
+    }
+    for (int64_t e = k; e < b && e < k + 4; ++e) {  // ragged end of the block
 #pragma unroll
         for (int i = 0; i < G; ++i) {
-            if (g0 + i >= nvec) break;
-            const double sy = block_sum_any<kRedBS>(ay[i], red);
-            if (threadIdx.x == 0) partials[(int64_t)(g0 + i) * nblk + blk] = sy;
-            if constexpr (TWO) {
-                const double sz = block_sum_any<kRedBS>(az[i], red);
-                if (threadIdx.x == 0) partials[(int64_t)(nvec + g0 + i) * nblk + blk] = sz;
+            ay[i] += (double)vp[i][e] * (double)y[e];
+            if constexpr (TWO) az[i] += (double)vp[i][e] * (double)z[e];
+        }
+    }
+    constexpr int kRep = 64 / GP;  // lanes that hold the same total
+    const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
+    const double ty = wave_sums<GP>(ay);
+    if (lane % kRep == 0) red[0][wv][lane / kRep] = ty;
+    if constexpr (TWO) {
+        const double tz = wave_sums<GP>(az);
+        if (lane % kRep == 0) red[1][wv][lane / kRep] = tz;
+    }
+    __syncthreads();
+    const int h = (int)threadIdx.x / 16, i = (int)threadIdx.x % 16;
+    if (h < (TWO ? 2 : 1) && i < cnt) {
+        double t = 0.0;
+#pragma unroll
+        for (int w = 0; w < kRedBS / 64; ++w) t += red[h][w][i];
+        partials[((int64_t)h * nvec + g0 + i) * nblk + blk] = t;
+    }
+    __syncthreads();
+}
+
+// partials[v * nblk + blk] = sum S_v Y; TWO: also sum S_v Z at
+// partials[(nvec + v) * nblk + blk].  The vectors go in groups of gs (<= GM, a
+// multiple of 4, or 2); blockIdx.y strides over the groups (one group per
+// workgroup for a small sector, whose workgroups would otherwise be too few).
+// HBM bound for large n; for a small one, by the chain of dependent loads.
+template <typename TX, int GM, bool TWO>
+__global__ __launch_bounds__(kRedBS) void k_dots(const TX *const *vecs, int nvec, int gs, const TX *y, const TX *z,
+                                                 int64_t n, double *partials, NormJob nj) {
+    __shared__ double red[TWO ? 2 : 1][kRedBS / 64][16];
+    __shared__ double sh[256];
+    const int nblk = gridDim.x, blk = blockIdx.x;
+    if (nj.n > 0 && blk == 0 && blockIdx.y == 0) norm_job(nj, sh);
+    int64_t a, b;
+    block_range(n, nblk, blk, a, b);
+    for (int g0 = gs * (int)blockIdx.y; g0 < nvec; g0 += gs * (int)gridDim.y) {
+        const int cnt = min(gs, nvec - g0);
+        if constexpr (GM == 2) {
+            dots_group<TX, 2, TWO>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
+        } else {
+            if (cnt <= 4) dots_group<TX, 4, TWO>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
+            else if (cnt <= 8) dots_group<TX, 8, TWO>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
+            else if constexpr (GM > 8) {
+                if (cnt <= 12) dots_group<TX, 12, TWO>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
+                else dots_group<TX, 16, TWO>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
             }
         }
     }
 }
 
-// Y = post * ((assign ? 0 : Y) - sum_i coef[i] S_i) as k_lincomb, four
-// elements per thread, four vectors' loads in flight.
+// U dots of the four elements w of a thread: lane l adds its share of the sum of
+// vector i to acc[g0 + i] of its wave (LDS).
+template <typename TX, int U>
+__device__ __forceinline__ void loc_batch(const TX *const *vecs, int g0, int cnt, int64_t k, int64_t b,
+                                          const double (&w)[4], double *acc) {
+    double d[U];
+    if (k + 4 <= b) {
+        Q4<TX> sv[U];
+#pragma unroll
+        for (int i = 0; i < U; ++i) sv[i] = load4(vecs[g0 + (i < cnt ? i : 0)] + k);
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            d[i] = (double)sv[i].v[0] * w[0];
+#pragma unroll
+            for (int e = 1; e < 4; ++e) d[i] += (double)sv[i].v[e] * w[e];
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < U; ++i) {
+            const TX *p = vecs[g0 + (i < cnt ? i : 0)];
+            d[i] = 0.0;
+            for (int e = 0; e < 4 && k + e < b; ++e) d[i] += (double)p[k + e] * w[e];
+        }
+    }
+    const double t = wave_sums<U>(d);
+    constexpr int kRep = 64 / U;
+    const int lane = (int)threadIdx.x & 63;
+    if (lane % kRep == 0 && lane / kRep < cnt) acc[g0 + lane / kRep] += t;
+}
+
+// partials[v * nblk + blk] = sum S_v W, W = Y less its first projection (LocalPass),
+// formed element by element in FP64.  A thread keeps W of its four elements in
+// registers and runs over the vectors, U at a time, each batch summed over the
+// wave at once (wave_sums) into the wave's LDS row: Y, S_j and S_{j-1} are read
+// once, whatever the number of vectors.  blockIdx.y splits the vectors where the
+// elements alone give too few workgroups.  Bound by HBM (or the Infinity Cache):
+// D = 853,776, FP64, 60 vectors on average: 79 us (5.3 TB/s), where two passes
+// with the vectors in groups of eight took 2 x 83 us (and 16 per group, W formed
+// again for each group, 104 us); D = 4900, 36 vectors: 2 x 24 us -> 6.8 us.
 template <typename TX>
-__global__ __launch_bounds__(kRedBS) void k_lincomb_v4(const TX *const *vecs, const double *coef, int nvec, TX *y,
-                                                       int64_t n, int assign, double sign, double *norm_part,
-                                                       const double *post_sig2) {
+__global__ __launch_bounds__(kRedBS) void k_dots_loc(const TX *const *vecs, int nvec, const TX *y, LocalPass lp,
+                                                     int64_t n, double *partials) {
+    constexpr int U = sizeof(TX) == 4 ? 16 : 8;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ double sh[256];
+    double *acc = reinterpret_cast<double *>(smem_raw);  // [waves][nvec]
+    const int nblk = gridDim.x, blk = blockIdx.x;
+    const int wv = (int)threadIdx.x >> 6;
+    for (int i = threadIdx.x; i < nvec * (kRedBS / 64); i += kRedBS) acc[i] = 0.0;
+    const double ca = lp.sig2[nvec - 1] * wg_sum_fixed(lp.part + (int64_t)(lp.nloc - 1) * nblk, nblk, sh);
+    double cb = 0.0;
+    const TX *sj = vecs[nvec - 1], *sk = sj;
+    if (lp.nloc > 1) {
+        cb = lp.sig2[nvec - 2] * wg_sum_fixed(lp.part, nblk, sh);
+        sk = vecs[nvec - 2];
+    }
+    if (blk == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+        lp.loc[0] = ca;
+        lp.loc[1] = cb;
+    }
+    const int per = ((nvec + (int)gridDim.y - 1) / (int)gridDim.y + 3) & ~3;
+    const int v0 = per * (int)blockIdx.y, v1 = min(nvec, v0 + per);
+    int64_t a, b;
+    block_range(n, nblk, blk, a, b);
+    for (int64_t k0 = a; k0 < b; k0 += 4 * kRedBS) {
+        const int64_t k = k0 + 4 * (int64_t)threadIdx.x;
+        double w[4] = {0.0, 0.0, 0.0, 0.0};
+        if (k + 4 <= b) {
+            const Q4<TX> yv = load4(y + k), jv = load4(sj + k), kv = load4(sk + k);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[e] = ((double)yv.v[e] - ca * (double)jv.v[e]) - cb * (double)kv.v[e];
+        } else {
+            for (int e = 0; e < 4 && k + e < b; ++e)
+                w[e] = ((double)y[k + e] - ca * (double)sj[k + e]) - cb * (double)sk[k + e];
+        }
+        int g = v0;
+        for (; g + U <= v1; g += U) loc_batch<TX, U>(vecs, g, U, k, b, w, acc + wv * nvec);
+        for (; g < v1; g += 4) loc_batch<TX, 4>(vecs, g, min(4, v1 - g), k, b, w, acc + wv * nvec);
+    }
+    __syncthreads();
+    for (int v = v0 + (int)threadIdx.x; v < v1; v += kRedBS) {
+        double t = 0.0;
+#pragma unroll
+        for (int q = 0; q < kRedBS / 64; ++q) t += acc[q * nvec + v];
+        partials[(int64_t)v * nblk + blk] = t;
+    }
+}
+
+// Coefficients of an update taken straight from partial sums instead of from a
+// finished array (no kernel in between): c_i = sig2[i] sum(part row i), plus the
+// first projection's loc[0] on the last vector and loc[1] on the one before;
+// *alpha = the last coefficient.
+struct DirectCoef {
+    const double *part = nullptr;
+    int nblk = 0;
+    const double *sig2 = nullptr, *loc = nullptr;
+    int nloc = 0;
+    double *alpha = nullptr;
+};
+
+// Y = post * ((assign ? 0 : Y) - sign * sum_i coef[i] S_i), four elements per
+// thread, U vectors' loads in flight; post = sqrt(*post_sig2) (1 if NULL).  With
+// norm_part, the partial sums of the stored result's norm.  SPLIT: the four
+// waves of a workgroup take every fourth vector of the same 256 elements (small
+// sectors); otherwise each wave has elements of its own.  Bound by HBM for large
+// n, by the chain of dependent load groups for small n.
+template <typename TX, bool SPLIT>
+__global__ __launch_bounds__(kRedBS) void k_update(const TX *const *vecs, const double *coef, DirectCoef dc, int nvec,
+                                                   TX *y, int64_t n, int assign, double sign, double *norm_part,
+                                                   const double *post_sig2) {
+    constexpr int U = SPLIT ? 8 : 4;
+    constexpr int NW = kRedBS / 64;
     __shared__ double c[kMaxVec];
     __shared__ const TX *p[kMaxVec];
-    __shared__ double red[kRedBS / 64];
-    for (int i = threadIdx.x; i < nvec; i += kRedBS) {
-        c[i] = sign * coef[i];
-        p[i] = vecs[i];
+    __shared__ double red[NW];
+    __shared__ double ps[SPLIT ? NW * 256 : 256];
+    if (dc.part) {
+        if (nvec <= 2) {
+            for (int v = 0; v < nvec; ++v) {
+                const double s = wg_sum_fixed(dc.part + (int64_t)v * dc.nblk, dc.nblk, ps);
+                if (threadIdx.x == 0) c[v] = dc.sig2[v] * s;
+            }
+        } else {
+            for (int i = threadIdx.x; i < nvec; i += kRedBS) {
+                double s = 0.0;
+                for (int q = 0; q < dc.nblk; ++q) s += dc.part[(int64_t)i * dc.nblk + q];
+                c[i] = dc.sig2[i] * s;
+            }
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            if (dc.nloc > 0) c[nvec - 1] += dc.loc[0];
+            if (dc.nloc > 1) c[nvec - 2] += dc.loc[1];
+            if (dc.alpha && blockIdx.x == 0) *dc.alpha = c[nvec - 1];
+        }
+    } else {
+        for (int i = threadIdx.x; i < nvec; i += kRedBS) c[i] = sign * coef[i];
     }
+    for (int i = threadIdx.x; i < nvec; i += kRedBS) p[i] = vecs[i];
     __syncthreads();
     int64_t a, b;
     block_range(n, gridDim.x, blockIdx.x, a, b);
     const double post = post_sig2 ? sqrt(*post_sig2) : 1.0;
     double nrm = 0.0;
-    int64_t k = a + 4 * (int64_t)threadIdx.x;
-    for (; k + 4 <= b; k += 4 * kRedBS) {
-        double v[4];
-        if (assign) {
+    if constexpr (SPLIT) {
+        const int lane = (int)threadIdx.x & 63, wv = (int)threadIdx.x >> 6;
+        for (int64_t k0 = a; k0 < b; k0 += 256) {
+            const int64_t k = k0 + 4 * lane;
+            double v[4] = {0.0, 0.0, 0.0, 0.0};
+            if (k + 4 <= b) {
+                int i = wv;
+                for (; i + (U - 1) * NW < nvec; i += U * NW) {
+                    Q4<TX> s4[U];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = 0.0;
-        } else {
-            const Q4<TX> q = load4(y + k);
+                    for (int t = 0; t < U; ++t) s4[t] = load4(p[i + t * NW] + k);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = (double)q.v[e];
+                    for (int t = 0; t < U; ++t)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) v[e] -= c[i + t * NW] * (double)s4[t].v[e];
+                }
+                for (; i < nvec; i += NW) {
+                    const Q4<TX> q = load4(p[i] + k);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] -= c[i] * (double)q.v[e];
+                }
+            } else {
+                for (int e = 0; e < 4 && k + e < b; ++e)
+                    for (int i = wv; i < nvec; i += NW) v[e] -= c[i] * (double)p[i][k + e];
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ps[wv * 256 + 4 * lane + e] = v[e];
+            __syncthreads();
+            const int64_t o = k0 + (int64_t)threadIdx.x;
+            if (o < b) {
+                double r = assign ? 0.0 : (double)y[o];
+#pragma unroll
+                for (int w = 0; w < NW; ++w) r += ps[w * 256 + (int)threadIdx.x];
+                const TX st = (TX)(post * r);
+                y[o] = st;
+                nrm += (double)st * (double)st;
+            }
+            __syncthreads();
         }
-        int i = 0;
-        for (; i + 4 <= nvec; i += 4) {
-            Q4<TX> s4[4];
+    } else {
+        int64_t k = a + 4 * (int64_t)threadIdx.x;
+        for (; k + 4 <= b; k += 4 * kRedBS) {
+            double v[4];
+            if (assign) {
 #pragma unroll
-            for (int t = 0; t < 4; ++t) s4[t] = load4(p[i + t] + k);
+                for (int e = 0; e < 4; ++e) v[e] = 0.0;
+            } else {
+                const Q4<TX> q = load4(y + k);
 #pragma unroll
-            for (int t = 0; t < 4; ++t)
+                for (int e = 0; e < 4; ++e) v[e] = (double)q.v[e];
+            }
+            int i = 0;
+            for (; i + U <= nvec; i += U) {
+                Q4<TX> s4[U];
 #pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] -= c[i + t] * (double)s4[t].v[e];
+                for (int t = 0; t < U; ++t) s4[t] = load4(p[i + t] + k);
+#pragma unroll
+                for (int t = 0; t < U; ++t)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) v[e] -= c[i + t] * (double)s4[t].v[e];
+            }
+            for (; i < nvec; ++i) {
+                const Q4<TX> q = load4(p[i] + k);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] -= c[i] * (double)q.v[e];
+            }
+            Q4<TX> o;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                o.v[e] = (TX)(post * v[e]);
+                nrm += (double)o.v[e] * (double)o.v[e];
+            }
+            store4(y + k, o);
         }
-        for (; i < nvec; ++i) {
-            const Q4<TX> q = load4(p[i] + k);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] -= c[i] * (double)q.v[e];
+        for (int64_t e = k; e < b && e < k + 4; ++e) {
+            double v = assign ? 0.0 : (double)y[e];
+            for (int i = 0; i < nvec; ++i) v -= c[i] * (double)p[i][e];
+            const TX st = (TX)(post * v);
+            y[e] = st;
+            nrm += (double)st * (double)st;
         }
-        Q4<TX> o;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            o.v[e] = (TX)(post * v[e]);
-            nrm += (double)o.v[e] * (double)o.v[e];
-        }
-        store4(y + k, o);
-    }
-    for (int64_t e = k; e < b && e < k + 4; ++e) {
-        double v = assign ? 0.0 : (double)y[e];
-        for (int i = 0; i < nvec; ++i) v -= c[i] * (double)p[i][e];
-        const TX st = (TX)(post * v);
-        y[e] = st;
-        nrm += (double)st * (double)st;
     }
     if (norm_part) {
         const double sm = block_sum_any<kRedBS>(nrm, red);
@@ -428,41 +612,23 @@ __global__ void k_scale(void *y, int64_t n, double f, int is_f32) {
     }
 }
 
-// Fixed-order sum of p[0..n), n <= 8 * 256, by one workgroup of 256: thread
-// t adds p[t], p[t + 256], ... in that order (all its loads issued at once),
-// then a shared-memory tree.  The result is valid in thread 0.
-__device__ __forceinline__ double wg_sum_fixed(const double *p, int n, double *sh) {
-    double v[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) {
-        const int i = (int)threadIdx.x + 256 * q;
-        v[q] = i < n ? p[i] : 0.0;
-    }
-    double s = 0.0;
-#pragma unroll
-    for (int q = 0; q < 8; ++q) s += v[q];
-    sh[threadIdx.x] = s;
-    __syncthreads();
-    for (int w = 128; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-        __syncthreads();
-    }
-    return sh[0];
-}
-
 // One workgroup per vector v (grid = nvec): raw[v] = sum of the v-th row of
-// partials, gamma[v] = sig2[v] raw[v]; the workgroup of v = jidx adds
-// gamma[jidx] to *alpha.
+// partials, gamma[v] = sig2[v] raw[v] plus the first projection's coefficient
+// (loc[0] on the last vector, loc[1] on the one before); the workgroup of
+// v = jidx sets *alpha = gamma[jidx].
 __global__ __launch_bounds__(256) void k_finalize_dots_par(const double *partials, int nblk, const double *sig2,
-                                                          double *raw, double *gamma, double *alpha, int jidx) {
+                                                          double *raw, double *gamma, double *alpha, int jidx,
+                                                          const double *loc, int nloc) {
     __shared__ double sh[256];
     const int v = blockIdx.x;
     const double s = wg_sum_fixed(partials + (int64_t)v * nblk, nblk, sh);
     if (threadIdx.x == 0) {
         if (raw) raw[v] = s;
-        const double g = (sig2 ? sig2[v] : 1.0) * s;
+        double g = (sig2 ? sig2[v] : 1.0) * s;
+        const int back = (int)gridDim.x - 1 - v;
+        if (back < nloc) g += loc[back];
         if (gamma) gamma[v] = g;
-        if (alpha && gamma && v == jidx) *alpha += g;
+        if (alpha && gamma && v == jidx) *alpha = g;
     }
 }
 
@@ -473,9 +639,11 @@ __global__ __launch_bounds__(256) void k_rowsums(const double *partials, int nbl
     if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
-// The coefficients of both projections from the row sums (reorth = 3): as
-// k_finalize_gram, with a[0..nvec) = <S_i, Y> and g = a[nvec..2 nvec) =
-// <S_i, S_jr> already summed.  One workgroup.
+// Coefficients of both projections from one two-sided multi-dot (reorth = 3),
+// whose row sums are given: a_i = <S_i, Y>, g_i = <S_i, S_jr> (jr = nvec - 1,
+// the newest vector).  Row jr of the Gram matrix G (ld x ld) is set from g, then
+// gamma1_i = sig2_i a_i, a2_i = a_i - sum_k G_ik gamma1_k, gamma_i = gamma1_i +
+// sig2_i a2_i, and *alpha = gamma_jr.  Fixed-order sums; one workgroup.
 __global__ __launch_bounds__(256) void k_gram_coef(const double *sums, int nvec, const double *sig2, double *gram,
                                                   int ld, double *gamma, double *alpha) {
     __shared__ double g1[kMaxVec];
@@ -492,83 +660,13 @@ __global__ __launch_bounds__(256) void k_gram_coef(const double *sums, int nvec,
         gamma[i] = g1[i] + sig2[i] * (sums[i] - t);
     }
     __syncthreads();
-    if (threadIdx.x == 0 && alpha) *alpha += gamma[jr];
+    if (threadIdx.x == 0 && alpha) *alpha = gamma[jr];
 }
 
-// Fixed-order sum of partials[v*nblk + 0..nblk) for each v; gamma[v] =
-// sig2[v] * sum.  If alpha != NULL, *alpha += gamma[jidx].
-__global__ void k_finalize_dots(const double *partials, int nvec, int nblk, const double *sig2, double *raw,
-                                double *gamma, double *alpha, int jidx) {
+// The norm of the last update by itself, where no later kernel of the run does it.
+__global__ void k_finalize_norm(NormJob nj) {
     __shared__ double sh[256];
-    for (int v = 0; v < nvec; ++v) {
-        double s = 0.0;
-        for (int i = threadIdx.x; i < nblk; i += 256) s += partials[(int64_t)v * nblk + i];
-        sh[threadIdx.x] = s;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            if (raw) raw[v] = sh[0];
-            if (gamma) gamma[v] = (sig2 ? sig2[v] : 1.0) * sh[0];
-        }
-        __syncthreads();
-    }
-    if (threadIdx.x == 0 && alpha && gamma) *alpha += gamma[jidx];
-}
-
-// Coefficients of both projections from one two-sided multi-dot (reorth = 3).
-// a_i = <S_i, Y>, g_i = <S_i, S_jr> (jr = nvec - 1, the newest vector): row jr
-// of the Gram matrix G (ld x ld) is set from g, then gamma1_i = sig2_i a_i,
-// a2_i = a_i - sum_k G_ik gamma1_k, gamma_i = gamma1_i + sig2_i a2_i, and
-// *alpha += gamma_jr.  Fixed-order sums; one workgroup of 256 threads.
-__global__ __launch_bounds__(256) void k_finalize_gram(const double *partials, int nvec, int nblk,
-                                                       const double *sig2, double *gram, int ld, double *gamma,
-                                                       double *alpha) {
-    __shared__ double sh[256];
-    __shared__ double av[kMaxVec], g1[kMaxVec];
-    const int jr = nvec - 1;
-    for (int v = 0; v < 2 * nvec; ++v) {
-        double s = 0.0;
-        for (int i = threadIdx.x; i < nblk; i += 256) s += partials[(int64_t)v * nblk + i];
-        sh[threadIdx.x] = s;
-        __syncthreads();
-        for (int w = 128; w > 0; w >>= 1) {
-            if ((int)threadIdx.x < w) sh[threadIdx.x] += sh[threadIdx.x + w];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) {
-            if (v < nvec) {
-                av[v] = sh[0];
-                g1[v] = sig2[v] * sh[0];
-            } else {
-                const int i = v - nvec;
-                gram[(int64_t)jr * ld + i] = sh[0];
-                gram[(int64_t)i * ld + jr] = sh[0];
-            }
-        }
-        __syncthreads();
-    }
-    for (int i = threadIdx.x; i < nvec; i += 256) {
-        double t = 0.0;
-        for (int k = 0; k < nvec; ++k) t += gram[(int64_t)i * ld + k] * g1[k];
-        gamma[i] = g1[i] + sig2[i] * (av[i] - t);
-    }
-    __syncthreads();
-    if (threadIdx.x == 0 && alpha) *alpha += gamma[jr];
-}
-
-// After the last update of step j the stored Y is w'' = sigma_j (Y - ...):
-// n2 = ||w''||^2 -> beta[j] = sqrt(n2), sig2[j+1] = 1/n2 (0 on exact breakdown).
-__global__ void k_finalize_norm(const double *partials, int nblk, double *sig2, double *beta, int jidx, int j) {
-    __shared__ double sh[256];
-    const double n2s = wg_sum_fixed(partials, nblk, sh);
-    if (threadIdx.x == 0) {
-        const double n2 = n2s;
-        beta[j] = sqrt(n2);
-        sig2[jidx + 1] = n2 > 0.0 ? 1.0 / n2 : 0.0;
-    }
+    norm_job(nj, sh);
 }
 
 __device__ int sturm_count(const double *al, const double *be, int m, double x, double pivmin) {
@@ -591,11 +689,9 @@ __device__ int sturm_count(const double *al, const double *be, int m, double x, 
 // count reaches 1 found by an LDS minimum), then thread 0 does inverse
 // iteration on T - theta I with one LU factorisation (partial pivoting) and
 // three solves; the running values of each recurrence stay in registers and
-// the factors in LDS.  `work` is unused (kept for the callers' layout).
+// the factors in LDS.
 static constexpr int kTriMax = 1024;
-__device__ void k_tridiag_lowest_body(const double *alpha, const double *beta, int m, double *out,
-                                      double *work) {
-    (void)work;
+__device__ void k_tridiag_lowest_body(const double *alpha, const double *beta, int m, double *out) {
     __shared__ double al[kTriMax], be[kTriMax];
     __shared__ double fd[kTriMax], fl[kTriMax], fu[kTriMax], fu2[kTriMax], z[kTriMax];
     __shared__ unsigned char piv[kTriMax];
@@ -729,9 +825,11 @@ __device__ void k_tridiag_lowest_body(const double *alpha, const double *beta, i
     for (int i = 0; i < m; ++i) out[3 + i] = sg * z[i];
 }
 
-__global__ __launch_bounds__(256) void k_tridiag_lowest(const double *alpha, const double *beta, int m,
-                                                        double unused, double *out, double *work) {
-    k_tridiag_lowest_body(alpha, beta, m, out, work);
+__global__ __launch_bounds__(256) void k_tridiag_lowest(const double *alpha, const double *beta, int m, double *out,
+                                                        NormJob nj) {
+    __shared__ double sh[256];
+    if (nj.n > 0) norm_job(nj, sh);  // beta[m - 1], read by the thread that writes it
+    k_tridiag_lowest_body(alpha, beta, m, out);
 }
 
 // coef[i] = s_i * sigma_i for the Ritz combination psi = sum_i s_i v_i
@@ -766,7 +864,9 @@ struct Work {
     std::vector<void *> locked;  // kmax locked-vector slots (may point into evecs)
     const void **vp = nullptr;   // device array of vector pointers [kmax + m + 1]
     double *sig2 = nullptr, *gamma = nullptr, *raw = nullptr, *alpha = nullptr, *beta = nullptr;
-    double *partials = nullptr, *tri = nullptr, *triwork = nullptr, *coef = nullptr;
+    double *partials = nullptr, *tri = nullptr, *coef = nullptr;
+    double *locpart = nullptr;   // partial sums of the first projection's dots (2 rows), then its two coefficients
+    double *npart = nullptr;     // partial sums of the newest vector's norm
     double *gram = nullptr;      // (m+1) x (m+1) Gram matrix of the stored vectors (reorth = 3)
     double *rcoef = nullptr;     // implicit-restart combination coefficients
 };
@@ -1008,10 +1108,11 @@ static size_t layout(Work &w, char *base, int64_t D, size_t elem, int m, int kma
     w.alpha = (double *)c.take((size_t)(m + 2) * sizeof(double));
     w.beta = (double *)c.take((size_t)(m + 2) * sizeof(double));
     w.partials = (double *)c.take((size_t)2 * nv * (size_t)w.nblk * sizeof(double));
+    w.locpart = (double *)c.take((2 * (size_t)w.nblk + 2) * sizeof(double));
+    w.npart = (double *)c.take((size_t)update_blocks(D) * sizeof(double));
     w.gram = (double *)c.take((size_t)(m + 1) * (size_t)(m + 1) * sizeof(double));
     w.rcoef = (double *)c.take((size_t)kIRMaxIn * kIRMaxOut * sizeof(double));
     w.tri = (double *)c.take((size_t)(m + 8) * sizeof(double));
-    w.triwork = (double *)c.take((size_t)(8 + 6 * (m + 2)) * sizeof(double) + (size_t)(m + 2) * sizeof(int) + 64);
     return c.off + 256;
 }
 
@@ -1027,39 +1128,78 @@ struct Solver {
     double moved = 0.0;  // algorithmic bytes of the vector kernels launched so far
     void count(double nvec) { moved += nvec * (double)h->D * (double)w.elem; }
 
+    NormJob pending;     // norm of the newest vector, not finished yet
+    NormJob take_norm() {
+        const NormJob j = pending;
+        pending = NormJob{};
+        return j;
+    }
+    // Small sectors: the kernels that follow the dots sum the partials themselves
+    // (16 rows or fewer per vector), which saves a launch of about 4 us.
+    bool few_partials() const { return w.nblk <= 16; }
+
+    template <typename TX, int GM, bool TWO>
+    void launch_dots(int vbeg, int nvec, const void *y, const void *z, double *out) {
+        // groups of about equal size (Y is read once per group)
+        const int ng = (nvec + GM - 1) / GM;
+        const int gs = GM == 2 ? 2 : std::min(GM, ((nvec + ng - 1) / ng + 3) & ~3);
+        // a workgroup per group while the element ranges alone are too few to
+        // fill the chip; large sectors loop over the groups inside, so that a
+        // range's Y comes from the caches for the second group on
+        const unsigned gy = w.nblk < 2048 ? (unsigned)((nvec + gs - 1) / gs) : 1u;
+        k_dots<TX, GM, TWO><<<dim3((unsigned)w.nblk, gy), kRedBS, 0, s>>>(
+            (const TX *const *)(w.vp + vbeg), nvec, gs, (const TX *)y, (const TX *)z, h->D, out, take_norm());
+        ED_LAUNCH_CHECK();
+    }
+    template <bool TWO>
+    void run_dots(int vbeg, int nvec, const void *y, const void *z, double *out) {
+        const bool f64 = h->prec == ED_FP64;
+        if constexpr (!TWO) {
+            if (nvec <= 2) {
+                if (f64) launch_dots<double, 2, TWO>(vbeg, nvec, y, z, out);
+                else launch_dots<float, 2, TWO>(vbeg, nvec, y, z, out);
+                return;
+            }
+        }
+        // FP64 keeps to 8 vectors (registers)
+        if (f64) launch_dots<double, 8, TWO>(vbeg, nvec, y, z, out);
+        else launch_dots<float, 16, TWO>(vbeg, nvec, y, z, out);
+    }
     template <typename TX>
-    void multidot(int vbeg, int nvec, const void *y) {
-        const TX *const *vecs = (const TX *const *)(w.vp + vbeg);
-        k_multidot_v4<TX, 8, false><<<w.nblk, kRedBS, 0, s>>>(vecs, nvec, (const TX *)y, nullptr, h->D, w.partials);
+    void launch_dots_loc(int nvec, const void *y, const LocalPass &lp) {
+        const int gy = std::max(1, std::min((nvec + 15) / 16, 512 / w.nblk));
+        k_dots_loc<TX><<<dim3((unsigned)w.nblk, (unsigned)gy), kRedBS, (size_t)nvec * 8 * (kRedBS / 64), s>>>(
+            (const TX *const *)w.vp, nvec, (const TX *)y, lp, h->D, w.partials);
         ED_LAUNCH_CHECK();
     }
     template <typename TX>
-    void lincomb(int vbeg, const double *coef, int nvec, void *y, int assign, double sign, double *normp,
-                 const double *post) {
+    void lincomb(int vbeg, const double *coef, const DirectCoef &dc, int nvec, void *y, int assign, double sign,
+                 double *normp, const double *post) {
         const TX *const *vecs = (const TX *const *)(w.vp + vbeg);
-        k_lincomb_v4<TX><<<w.nblk, kRedBS, 0, s>>>(vecs, coef, nvec, (TX *)y, h->D, assign, sign, normp, post);
+        const int nb = update_blocks(h->D);
+        if (h->D <= kSplitMax)
+            k_update<TX, true><<<nb, kRedBS, 0, s>>>(vecs, coef, dc, nvec, (TX *)y, h->D, assign, sign, normp, post);
+        else
+            k_update<TX, false><<<nb, kRedBS, 0, s>>>(vecs, coef, dc, nvec, (TX *)y, h->D, assign, sign, normp, post);
         ED_LAUNCH_CHECK();
     }
+    void lincomb_any(int vbeg, const double *coef, const DirectCoef &dc, int nvec, void *y, int assign, double sign,
+                     double *normp, const double *post) {
+        if (h->prec == ED_FP64) lincomb<double>(vbeg, coef, dc, nvec, y, assign, sign, normp, post);
+        else lincomb<float>(vbeg, coef, dc, nvec, y, assign, sign, normp, post);
+    }
+    // one full pass: gamma_i = sigma_i^2 <S_i, y>
     void dots(int vbeg, int nvec, const void *y, double *alpha, int jrel) {
         count(nvec + 1);
-        if (h->prec == ED_FP64) multidot<double>(vbeg, nvec, y);
-        else multidot<float>(vbeg, nvec, y);
+        run_dots<false>(vbeg, nvec, y, nullptr, w.partials);
         k_finalize_dots_par<<<nvec, 256, 0, s>>>(w.partials, w.nblk, w.sig2 + vbeg, w.raw, w.gamma + vbeg, alpha,
-                                                 jrel);
+                                                 jrel, nullptr, 0);
         ED_LAUNCH_CHECK();
     }
     // both projections of one step from a single read of the basis (reorth = 3)
     void dots_gram(int nvec, const void *y, const void *z, double *alpha) {
         count(nvec + 2);
-        if (h->prec == ED_FP64)
-            k_multidot_v4<double, 8, true><<<w.nblk, kRedBS, 0, s>>>((const double *const *)w.vp, nvec,
-                                                                    (const double *)y, (const double *)z, h->D,
-                                                                    w.partials);
-        else
-            k_multidot_v4<float, 8, true><<<w.nblk, kRedBS, 0, s>>>((const float *const *)w.vp, nvec,
-                                                                   (const float *)y, (const float *)z, h->D,
-                                                                   w.partials);
-        ED_LAUNCH_CHECK();
+        run_dots<true>(0, nvec, y, z, w.partials);
         k_rowsums<<<2 * nvec, 256, 0, s>>>(w.partials, w.nblk, w.raw);
         ED_LAUNCH_CHECK();
         k_gram_coef<<<1, 256, 0, s>>>(w.raw, nvec, w.sig2, w.gram, w.m + 1, w.gamma, alpha);
@@ -1067,13 +1207,56 @@ struct Solver {
     }
     void update(int vbeg, int nvec, void *y, double *normp, const double *post = nullptr) {
         count(nvec + 2);
-        if (h->prec == ED_FP64) lincomb<double>(vbeg, w.gamma + vbeg, nvec, y, 0, 1.0, normp, post);
-        else lincomb<float>(vbeg, w.gamma + vbeg, nvec, y, 0, 1.0, normp, post);
+        lincomb_any(vbeg, w.gamma + vbeg, DirectCoef{}, nvec, y, 0, 1.0, normp, post);
+    }
+    // Gram-Schmidt of Y = H S_j against the locked vectors and S_0..S_j, scaled by
+    // sigma_j: leaves S_{j+1} in Y, alpha_j in alpha[j] and the norm as pending.
+    void orthogonalise(int j, void *Y, const void *sj) {
+        const int nv = nlock + j + 1, nloc = std::min(j + 1, 2);
+        double *al = w.alpha + j;
+        const double *post = w.sig2 + nlock + j;
+        const int vl = nv - nloc;  // S_{j-1} (when there is one) and S_j
+        if (o.reorth == 3 && nlock == 0) {
+            dots_gram(nv, Y, sj, al);
+            update(0, nv, Y, w.npart, post);
+        } else if (o.reorth == 1 || (o.reorth == 0 && nlock > 0 && j < 2)) {
+            dots(0, nv, Y, al, nv - 1);
+            update(0, nv, Y, w.npart, post);
+        } else {
+            count(nloc + 1);
+            run_dots<false>(vl, nloc, Y, nullptr, w.locpart);
+            if (o.reorth == 0) {  // three-term recurrence: nothing more to project on
+                count(nloc + 2);
+                lincomb_any(vl, nullptr, DirectCoef{w.locpart, w.nblk, w.sig2 + vl, nullptr, 0, al}, nloc, Y, 0, 1.0,
+                            w.npart, post);
+            } else {
+                double *loc = w.locpart + 2 * (size_t)w.nblk;
+                count(nv + 1);
+                const LocalPass lp{w.locpart, w.sig2, nloc, loc};
+                if (h->prec == ED_FP64) launch_dots_loc<double>(nv, Y, lp);
+                else launch_dots_loc<float>(nv, Y, lp);
+                count(nv + 2);
+                if (few_partials()) {
+                    lincomb_any(0, nullptr, DirectCoef{w.partials, w.nblk, w.sig2, loc, nloc, al}, nv, Y, 0, 1.0,
+                                w.npart, post);
+                } else {
+                    k_finalize_dots_par<<<nv, 256, 0, s>>>(w.partials, w.nblk, w.sig2, nullptr, w.gamma, al, nv - 1,
+                                                           loc, nloc);
+                    ED_LAUNCH_CHECK();
+                    lincomb_any(0, w.gamma, DirectCoef{}, nv, Y, 0, 1.0, w.npart, post);
+                }
+            }
+        }
+        pending = NormJob{w.npart, update_blocks(h->D), w.sig2 + nlock + j + 1, w.beta + j};
+    }
+    // lowest eigenpair of T_m, after the norm of the last step if that is pending
+    void tridiag_lowest(int m) {
+        k_tridiag_lowest<<<1, 256, 0, s>>>(w.alpha, w.beta, m, w.tri, take_norm());
+        ED_LAUNCH_CHECK();
     }
     void combine(int vbeg, const double *coef, int nvec, void *out) {  // out = sum coef_i S_i
         count(nvec + 1);
-        if (h->prec == ED_FP64) lincomb<double>(vbeg, coef, nvec, out, 1, -1.0, nullptr, nullptr);
-        else lincomb<float>(vbeg, coef, nvec, out, 1, -1.0, nullptr, nullptr);
+        lincomb_any(vbeg, coef, DirectCoef{}, nvec, out, 1, -1.0, nullptr, nullptr);
     }
     void upload_pointers(const std::vector<void *> &krylov) {
         std::vector<const void *> v;
@@ -1101,9 +1284,8 @@ struct Solver {
     // vector norm^2 of y via a one-vector multidot with pointer slot `idx`
     double norm2_sync(int idx, const void *y) {
         count(1);
-        if (h->prec == ED_FP64) multidot<double>(idx, 1, y);
-        else multidot<float>(idx, 1, y);
-        k_finalize_dots_par<<<1, 256, 0, s>>>(w.partials, w.nblk, nullptr, w.raw, nullptr, nullptr, 0);
+        run_dots<false>(idx, 1, y, nullptr, w.partials);
+        k_finalize_dots_par<<<1, 256, 0, s>>>(w.partials, w.nblk, nullptr, w.raw, nullptr, nullptr, 0, nullptr, 0);
         ED_LAUNCH_CHECK();
         double r = 0.0;
         ED_HIP(hipMemcpyAsync(&r, w.raw, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -1158,7 +1340,7 @@ struct Solver {
             launch_restart_combine<float>((const float *const *)w.vp + nlock, w.rcoef, nin, nout, h->D, w.partials,
                                           w.nblk, s);
         ED_LAUNCH_CHECK();
-        k_finalize_dots_par<<<1, 256, 0, s>>>(w.partials, w.nblk, nullptr, w.raw, nullptr, nullptr, 0);
+        k_finalize_dots_par<<<1, 256, 0, s>>>(w.partials, w.nblk, nullptr, w.raw, nullptr, nullptr, 0, nullptr, 0);
         ED_LAUNCH_CHECK();
         double n2 = 0.0;
         ED_HIP(hipMemcpyAsync(&n2, w.raw, sizeof(double), hipMemcpyDeviceToHost, s));
@@ -1205,27 +1387,11 @@ struct Solver {
         for (int j = 0; j < m; ++j) {
             void *Y = kr[j + 1];
             apply_launch(h, kr[j], Y, s);
-                count(2);
-            const int nv = j + 1;
-            if (o.reorth == 3) {
-                dots_gram(nv, Y, kr[j], w.alpha + j);
-                update(0, nv, Y, w.partials, w.sig2 + j);
-            } else {
-                int vb = 0, nvec = nv;
-                if (o.reorth == 0 && j >= 2) {
-                    vb = j - 1;
-                    nvec = 2;
-                }
-                const int passes = o.reorth >= 2 ? 2 : 1;
-                for (int ps = 0; ps < passes; ++ps) {
-                    const bool last_pass = ps == passes - 1;
-                    dots(vb, nvec, Y, w.alpha + j, j - vb);
-                    update(vb, nvec, Y, last_pass ? w.partials : nullptr, last_pass ? w.sig2 + j : nullptr);
-                }
-            }
-            k_finalize_norm<<<1, 256, 0, s>>>(w.partials, w.nblk, w.sig2, w.beta, j, j);
-            ED_LAUNCH_CHECK();
+            count(2);
+            orthogonalise(j, Y, kr[j]);
         }
+        k_finalize_norm<<<1, 256, 0, s>>>(take_norm());
+        ED_LAUNCH_CHECK();
         ED_HIP(hipMemcpyAsync(alpha_h, w.alpha, (size_t)m * sizeof(double), hipMemcpyDeviceToHost, s));
         ED_HIP(hipMemcpyAsync(beta_h, w.beta, (size_t)m * sizeof(double), hipMemcpyDeviceToHost, s));
         ED_HIP(hipStreamSynchronize(s));
@@ -1303,35 +1469,12 @@ struct Solver {
                 void *Y = kr[j + 1];
                 apply_launch(h, kr[j], Y, s);
                 count(2);
-                const int nv = nlock + j + 1;
-                int vb = 0, nvec = nv;
-                if (o.reorth == 0 && j >= 2) {  // three-term recurrence by projection on S_{j-1}, S_j
-                    vb = nlock + j - 1;
-                    nvec = 2;
-                }
-                if (o.reorth == 3 && nlock == 0) {
-                    // one two-sided multi-dot (Y and S_j) and one update with the
-                    // coefficients of both projections; scaled by sigma_j like below
-                    dots_gram(nv, Y, kr[j], w.alpha + j);
-                    update(0, nv, Y, w.partials, w.sig2 + j);
-                } else {
-                    const int passes = o.reorth >= 2 ? 2 : 1;
-                    for (int ps = 0; ps < passes; ++ps) {
-                        const bool last_pass = ps == passes - 1;
-                        dots(vb, nvec, Y, w.alpha + j, nlock + j - vb);
-                        // the last pass also scales by sigma_j: the stored vector is w''
-                        update(vb, nvec, Y, last_pass ? w.partials : nullptr,
-                               last_pass ? w.sig2 + nlock + j : nullptr);
-                    }
-                }
-                k_finalize_norm<<<1, 256, 0, s>>>(w.partials, w.nblk, w.sig2, w.beta, nlock + j, j);
-                ED_LAUNCH_CHECK();
+                orthogonalise(j, Y, kr[j]);
                 ++total;
                 const bool full = (j + 1 == m);
                 const bool check = j == 0 || ((j + 1) % o.check_every == 0) || full || total >= o.max_iter;
                 if (!check) continue;
-                k_tridiag_lowest<<<1, 256, 0, s>>>(w.alpha, w.beta, j + 1, 0.0, w.tri, w.triwork);
-                ED_LAUNCH_CHECK();
+                tridiag_lowest(j + 1);
                 double tv[3];
                 ED_HIP(hipMemcpyAsync(tv, w.tri, sizeof(tv), hipMemcpyDeviceToHost, s));
                 ED_HIP(hipStreamSynchronize(s));
@@ -1367,8 +1510,7 @@ struct Solver {
                 jstart = o.keep;
                 if (brk_ir) {
                     // the kept vectors span an invariant subspace: finish on them
-                    k_tridiag_lowest<<<1, 256, 0, s>>>(w.alpha, w.beta, jstart, 0.0, w.tri, w.triwork);
-                    ED_LAUNCH_CHECK();
+                    tridiag_lowest(jstart);
                     jlast = jstart;
                     converged = true;
                     k_ritz_coef<<<1, 256, 0, s>>>(w.tri + 3, w.sig2 + nlock, jlast, w.coef);

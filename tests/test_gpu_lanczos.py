@@ -274,3 +274,27 @@ def test_lowest_more_continues_from_converged_levels(prec):
     assert np.max(np.abs(V @ V.T - np.eye(10))) < (1e-8 if prec == 0 else 1e-4)
     with pytest.raises(ed.EDError):
         H.lowest_more(10, 10, E10, _v0(b.D, prec), e10, o)
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("ns,nn,basis,keep", [
+    (3, (1, 1), 9, 0),        # D = 9: one ragged group of elements
+    (7, (3, 2), 40, 8),       # D = 735: one workgroup, ragged end
+    (8, (4, 4), 120, 0),      # D = 4900: coefficients from the partial sums, vectors split over the waves
+    (9, (5, 4), 33, 8),       # D = 15,876: the most partial sums an update adds up itself
+    (10, (5, 4), 34, 0),      # D = 52,920: finished coefficients, vectors split over the waves
+    (11, (6, 5), 35, 8),      # D = 213,444: a wave's own elements
+], ids=["d9", "d735", "d4900", "d15876", "d52920", "d213444"])
+def test_two_pass_reorthogonalisation_sizes(ns, nn, basis, keep, prec):
+    """reorth = 2 at the sizes where its kernels change their split: the two
+    lowest levels (the second one deflated, so the vector tables start with a
+    locked vector) against the oracle."""
+    ed = gpu_ed()
+    phys = wl.aim(ns - 1, 2.0, -1.0, seed=40 + ns)
+    b, H = build(phys, *nn, prec)
+    e_ref = orc.lowest_k(sector(phys, *nn), 2, tol=1e-13)
+    E, info = H.lowest(2, _v0(b.D, prec, 5), ed.options(tol=1e-10 if prec == 0 else 1e-7, reorth=2, max_basis=basis,
+                                                        keep=keep, max_iter=3000))
+    assert all(i["converged"] == 1 for i in info)
+    for a, r in zip(E, e_ref):
+        assert _rel(a, r) <= TOL[prec], (E, e_ref)
