@@ -298,3 +298,26 @@ def test_two_pass_reorthogonalisation_sizes(ns, nn, basis, keep, prec):
     assert all(i["converged"] == 1 for i in info)
     for a, r in zip(E, e_ref):
         assert _rel(a, r) <= TOL[prec], (E, e_ref)
+
+
+@pytest.mark.parametrize("m,reorth", [(1, 3), (2, 3), (3, 3), (5, 3), (6, 3), (44, 3), (100, 3), (301, 0)])
+def test_tridiagonal_lowest_eigenpair(m, reorth):
+    """The device eigensolve of T_m against numpy: theta to the rounding of T,
+    the residual estimate |beta_m s_m| to that of the eigenvector's last
+    component (301 three-term steps hold several copies of the lowest value:
+    theta only)."""
+    ed = gpu_ed()
+    phys = wl.aim(7, 2.0, -1.0, seed=21)
+    b, H = build(phys, 4, 4, 0)
+    v0 = _v0(b.D, 0, 9)
+    a, be, _ = H.lanczos_tridiag(v0, m, ed.options(reorth=reorth))
+    assert len(a) == m
+    E, info = H.lanczos_ground(v0, ed.options(max_iter=m, max_basis=max(m, 2), check_every=1000, tol=1e-200, refine=0,
+                                              reorth=reorth), allow_noconv=True)
+    assert info["iters"] == m
+    w, z = np.linalg.eigh(np.diag(a) + np.diag(be[:m - 1], 1) + np.diag(be[:m - 1], -1))
+    eps, nrm = 2.0 ** -52, np.max(np.abs(w))
+    assert abs(E - w[0]) <= 16 * eps * nrm, (E, w[0])
+    if reorth == 3:
+        gap = w[1] - w[0] if m > 1 else nrm
+        assert abs(info["residual"] - abs(be[m - 1] * z[-1, 0])) <= 64 * eps * nrm / gap * be[m - 1]
