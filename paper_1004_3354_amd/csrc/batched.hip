@@ -22,6 +22,7 @@
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
+#include <memory>
 #include <thread>
 #include <vector>
 
@@ -50,6 +51,12 @@ struct BSec {
     // rank, down move table, amplitude with the up sign), CSR over up ranks
     const int32_t *xl_off, *xl_src, *xl_tab;
     const TA *xl_amp;
+    // row tiles: four-state packed down hops, distinct amplitudes, and the list
+    // strides of a row (hop slots a multiple of four, four-fermion slots)
+    const int32_t *dn_ell4_off;
+    const uint4 *dn_ell4;
+    const TA *amp_tab;
+    int namp, um, xm;
     int nch;       // reduction chunks of this sector
     int64_t pbase; // offset of this sector's partials
 };
@@ -229,6 +236,209 @@ __global__ __launch_bounds__(kBBS) void kb_apply(const BSec<TX, TA> *secs, const
         if (threadIdx.x == 0) {
             tpart[2 * (int64_t)blockIdx.x] = s0;
             tpart[2 * (int64_t)blockIdx.x + 1] = s1;
+        }
+    }
+}
+
+// The step's apply for sectors with packed down hops: slot (j+1) = H slot j.  A
+// tile is nr <= kBRows whole rows of one sector in groups of R (one LDS read of
+// 16 bytes returns a column's values for a group), with the rows' hop and
+// four-fermion lists staged next to them; a work item is four columns of a group,
+// so a hop table word (four columns, 16 bytes) and the column data serve 4 R
+// outputs and up-spin partners are 16-byte loads.  kb_apply, one column of four
+// rows per item over the CSR tables, needs four to eight times the loads per
+// output: all 169 sectors of the 12-site impurity (1.7e7 elements, FP32), 297 us
+// -> about 125 us per step.  Bound by the latency of its dependent loads: tiles of
+// 4096 elements (one work item per thread) beat 2048, 8192 and 16384, and six
+// waves per SIMD (register bound) beat four by 3 % of the whole step.
+template <typename TX>
+static constexpr int kBR = 16 / (int)sizeof(TX);
+
+template <typename T>
+__device__ __forceinline__ typename V4<T>::t ld_cols(const T *p, int n, T fill) {
+    if (n >= 4) return ld4(p);
+    typename V4<T>::t v = {fill, fill, fill, fill};
+#pragma unroll
+    for (int j = 0; j < 3; ++j)
+        if (j < n) v[j] = p[j];
+    return v;
+}
+
+template <typename TX>
+__global__ __launch_bounds__(kBBS, sizeof(TX) == 4 ? 6 : 4) void kb_tile(const BSec<TX, TX> *secs, const ATile *tiles, const int *jcur,
+                                                const int *active) {
+    constexpr int R = kBR<TX>;
+    using RVt = typename RV<TX, R>::t;
+    using V = typename V4<TX>::t;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ TX s_e[kBRows], s_xt[256];
+    __shared__ uint32_t s_su[kBRows], s_cu[kBRows];
+    __shared__ int32_t s_nu[kBRows], s_nx[kBRows];
+    const ATile tl = tiles[blockIdx.x];
+    if (active[tl.sec] != 1) return;
+    const BSec<TX, TX> &S = secs[tl.sec];
+    const int j = jcur[tl.sec];
+    const TX *x = S.base + (int64_t)j * S.D;
+    TX *y = S.base + (int64_t)(j + 1) * S.D;
+    const uint32_t ddn = (uint32_t)S.ddn, u0 = (uint32_t)tl.u0;
+    const int nr = tl.nr, nrg = (nr + R - 1) / R, um = S.um, xm = S.xm;
+    TX *xs = reinterpret_cast<TX *>(smem_raw);   // [nrg][ddn][R]
+    TX *amps = xs + (size_t)nrg * R * ddn;       // [namp]
+    TX *ua = amps + S.namp, *xa = ua + nr * um;  // [nr][um], [nr][xm]
+    int32_t *ut = reinterpret_cast<int32_t *>(xa + nr * xm), *xsr = ut + nr * um, *xtb = xsr + nr * xm;
+    const uint32_t nq = (ddn + 3) / 4, ni = (uint32_t)nrg * nq;
+    const int tid = (int)threadIdx.x;
+    for (uint32_t k = tid; k < ni; k += kBBS) {
+        const uint32_t g = k / nq, c = 4 * (k - g * nq);
+        const int n = (int)min(4u, ddn - c);
+        V v[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int row = min((int)(g * R) + r, nr - 1);
+            v[r] = ld_cols(x + (int64_t)(u0 + row) * ddn + c, n, (TX)0);
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            if (q >= n) break;
+            RVt o;
+#pragma unroll
+            for (int r = 0; r < R; ++r) o[r] = v[r][q];
+            *reinterpret_cast<RVt *>(xs + ((size_t)g * ddn + c + q) * R) = o;
+        }
+    }
+    for (int k = tid; k < S.namp; k += kBBS) amps[k] = S.amp_tab[k];
+    if (S.koff)
+        for (int k = tid; k < (1 << (2 * S.koff)); k += kBBS) s_xt[k] = S.xtab[k];
+    for (int r = tid; r < nr; r += kBBS) {
+        const uint32_t u = u0 + (uint32_t)r;
+        s_e[r] = S.up_e[u];
+        s_su[r] = S.up_st[u] & S.umask;
+        s_cu[r] = S.koff ? (uint32_t)S.up_c[u] << S.koff : 0u;
+        s_nu[r] = S.up_off[u + 1] - S.up_off[u];
+        s_nx[r] = S.nx ? S.xl_off[u + 1] - S.xl_off[u] : 0;
+    }
+    for (int k = tid; k < nr * um; k += kBBS) {
+        const int r = k / um, i = k - r * um;
+        const int32_t b = S.up_off[u0 + r], n = S.up_off[u0 + r + 1] - b;
+        ut[k] = i < n ? S.up_tgt[b + i] : (int32_t)u0 + r;  // unused slots: the row itself, amplitude 0
+        ua[k] = i < n ? S.up_sa[b + i] : (TX)0;
+    }
+    for (int k = tid; k < nr * xm; k += kBBS) {
+        const int r = k / xm, i = k - r * xm;
+        const int32_t b = S.xl_off[u0 + r], n = S.xl_off[u0 + r + 1] - b;
+        if (i < n) {
+            xsr[k] = S.xl_src[b + i];
+            xtb[k] = S.xl_tab[b + i];
+            xa[k] = S.xl_amp[b + i];
+        }
+    }
+    __syncthreads();
+    for (uint32_t k = tid; k < ni; k += kBBS) {
+        const uint32_t g = k / nq, q = k - g * nq, c = 4 * q;
+        const int n = (int)min(4u, ddn - c), r0 = (int)(g * R);
+        const V ed = ld_cols(S.dn_e + c, n, (TX)0);
+        const typename V4<uint32_t>::t st = ld_cols(S.dn_st + c, n, 0u);
+        const TX *xg = xs + (size_t)g * ddn * R;
+        TX acc[R][4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t d = min(c + e, ddn - 1);
+            const uint32_t cd = S.koff ? (uint32_t)S.dn_c[d] : 0u;
+            const RVt v = *reinterpret_cast<const RVt *>(xg + d * R);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int row = min(r0 + r, nr - 1);
+                TX w = (TX)0;
+                if (S.umode == 1) w = S.U0 * (TX)__popc(s_su[row] & st[e]);
+                else if (S.umode == 2) {
+                    uint32_t mm = s_su[row] & st[e];
+                    while (mm) {
+                        w += S.usite[__ffs(mm) - 1];
+                        mm &= mm - 1u;
+                    }
+                }
+                if (S.koff) w += s_xt[s_cu[row] | cd];
+                acc[r][e] = (s_e[row] + ed[e] + w) * v[r];
+            }
+        }
+        // 1 (x) H_dn
+        {
+            const int32_t eb = S.dn_ell4_off[q >> 6], kk = (S.dn_ell4_off[(q >> 6) + 1] - eb) >> 6;
+            const uint4 *ep = S.dn_ell4 + eb + (q & 63u);
+#pragma unroll 2
+            for (int32_t h = 0; h < kk; ++h) {
+                const uint4 w = ep[h * 64];
+                const uint32_t ev[4] = {w.x, w.y, w.z, w.w};
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const TX am = amps[ev[e] >> 20];
+                    const RVt v = *reinterpret_cast<const RVt *>(xg + (ev[e] & 0xFFFFFu) * R);
+#pragma unroll
+                    for (int r = 0; r < R; ++r) acc[r][e] += am * v[r];
+                }
+            }
+        }
+        // H_up (x) 1, four partner rows at a time
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r0 + r >= nr) break;
+            const int32_t *tp = ut + (r0 + r) * um;
+            const TX *ap = ua + (r0 + r) * um;
+            for (int h = 0; h < s_nu[r0 + r]; h += 4) {
+                V v[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) v[i] = ld_cols(x + (int64_t)tp[h + i] * ddn + c, n, (TX)0);
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) acc[r][e] += ap[h + i] * v[i][e];
+            }
+        }
+        // four-fermion terms: the rows' i-th terms together
+        if (xm > 0) {
+            int kx = 0;
+#pragma unroll
+            for (int r = 0; r < R; ++r) kx = max(kx, r0 + r < nr ? s_nx[r0 + r] : 0);
+            for (int i = 0; i < kx; ++i) {
+                typename V4<int32_t>::t m[R];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    m[r] = typename V4<int32_t>::t{-1, -1, -1, -1};
+                    if (r0 + r < nr && i < s_nx[r0 + r])
+                        m[r] = ld_cols(S.dn_mv + (int64_t)xtb[(r0 + r) * xm + i] * ddn + c, n, (int32_t)-1);
+                }
+                TX v[R][4];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const TX *src = x + (int64_t)xsr[min(r0 + r, nr - 1) * xm + i] * ddn;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) {
+                        v[r][e] = (TX)0;
+                        if (m[r][e] >= 0) v[r][e] = src[m[r][e] >> 1];
+                    }
+                }
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const TX am = xa[min(r0 + r, nr - 1) * xm + i];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (m[r][e] >= 0) acc[r][e] += (m[r][e] & 1) ? -am * v[r][e] : am * v[r][e];
+                }
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (r0 + r >= nr) break;
+            TX *yr = y + (int64_t)(u0 + r0 + r) * ddn + c;
+            if (n == 4) {
+                V o;
+                o.x = acc[r][0]; o.y = acc[r][1]; o.z = acc[r][2]; o.w = acc[r][3];
+                st4<TX, false>(yr, o);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 3; ++e)
+                    if (e < n) yr[e] = acc[r][e];
+            }
         }
     }
 }
@@ -781,12 +991,59 @@ static BSec<TX, TA> make_bsec(const ed_ham_s *h, TX *base, int nch, int64_t pbas
     b.xl_src = h->nx ? h->xl_src.as<int32_t>() : nullptr;
     b.xl_tab = h->nx ? h->xl_tab.as<int32_t>() : nullptr;
     b.xl_amp = h->nx ? (const TA *)(dbl ? h->xl_amp64.p : h->xl_amp32.p) : nullptr;
+    b.dn_ell4_off = Dn.ell4_off.as<int32_t>();
+    b.dn_ell4 = Dn.ell4.as<uint4>();
+    b.amp_tab = (const TA *)(dbl ? Dn.amp64.p : Dn.amp32.p);
+    b.namp = Dn.namp;
+    b.um = (U.max_hops + 3) & ~3;
+    b.xm = h->nx ? h->xl_max : 0;
     b.nch = nch;
     b.pbase = pbase;
     return b;
 }
 
-static std::vector<ATile> make_tiles(const Batch &B, int64_t tile, size_t elem, size_t *lds_max) {
+// LDS bytes of a row tile of nr rows (kb_tile).
+static size_t row_tile_lds(const ed_ham_s *h, int nr, size_t elem) {
+    const int R = 16 / (int)elem;
+    const size_t um = (size_t)((h->sp[0].max_hops + 3) & ~3), xm = h->nx ? (size_t)h->xl_max : 0;
+    return (size_t)((nr + R - 1) / R) * R * (size_t)h->ddn * elem + (size_t)h->sp[1].namp * elem +
+           (size_t)nr * (um * (elem + 4) + xm * (elem + 8));
+}
+static constexpr size_t kRowTileLds = 60 * 1024;
+// Sectors kb_tile takes: packed down hops, the cross table in LDS, one group of
+// rows in LDS.  The others (no down hops at all, very long rows) go to kb_apply.
+static bool row_tile_fits(const ed_ham_s *h, size_t elem) {
+    return h->sp[1].pk_ok && h->koff <= 4 &&
+           row_tile_lds(h, (int)std::min<int64_t>(16 / (int64_t)elem, h->dup), elem) <= kRowTileLds;
+}
+
+// Row tiles of about `tile` elements: whole groups of rows, at most kBRows.
+static std::vector<ATile> make_row_tiles(const Batch &B, int64_t tile, size_t elem, size_t *lds_max) {
+    std::vector<ATile> t;
+    size_t lmax = 0;
+    const int64_t R = 16 / (int64_t)elem;
+    std::vector<int> order(B.nsec);
+    for (int s = 0; s < B.nsec; ++s) order[s] = s;
+    std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return B.D[a] > B.D[b]; });
+    for (int s : order) {
+        const ed_ham_s *h = B.hs[s];
+        if (!row_tile_fits(h, elem)) continue;
+        int64_t nr = std::max<int64_t>(R, std::min<int64_t>(tile / std::max<int64_t>(h->ddn, 1) / R * R, kBRows));
+        nr = std::min(nr, h->dup);
+        while (nr > R && row_tile_lds(h, (int)nr, elem) > kRowTileLds) nr -= R;
+        nr = std::max<int64_t>(1, nr);
+        for (int64_t u0 = 0; u0 < h->dup; u0 += nr) {
+            const int n = (int)std::min<int64_t>(nr, h->dup - u0);
+            lmax = std::max(lmax, row_tile_lds(h, n, elem));
+            t.push_back(ATile{s, (int32_t)u0, n, 1});
+        }
+    }
+    *lds_max = lmax;
+    return t;
+}
+
+// skip_row: leave out the sectors kb_tile takes.
+static std::vector<ATile> make_tiles(const Batch &B, int64_t tile, size_t elem, bool skip_row, size_t *lds_max) {
     std::vector<ATile> t;
     size_t lmax = 0;
     const size_t budget = 64 * 1024;
@@ -796,6 +1053,7 @@ static std::vector<ATile> make_tiles(const Batch &B, int64_t tile, size_t elem, 
     std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return B.D[a] > B.D[b]; });
     for (int s : order) {
         const ed_ham_s *h = B.hs[s];
+        if (skip_row && row_tile_fits(h, elem)) continue;
         int64_t R = std::max<int64_t>(1, tile / std::max<int64_t>(h->ddn, 1));
         R = std::min<int64_t>(std::min<int64_t>(R, h->dup), kBRows);
         for (int64_t u0 = 0; u0 < h->dup; u0 += R) {
@@ -921,28 +1179,44 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     ED_HIP(hipStreamSynchronize(s));
 
     // ---- tile schedule: time a few tile sizes on slot 0 -> slot 1 (every sector at step 0)
-    std::vector<int64_t> cands = {2048, 8192, 32768, 131072};
+    std::vector<int64_t> cands = {2048, 4096, 8192, 16384};
     if (const char *env = std::getenv("ED_BATCH_TILE")) cands = {std::max<int64_t>(64, std::atoll(env))};
-    std::vector<ATile> best_tiles;
     int64_t best_tile_size = 0;
-    size_t best_lds = 0;
     float best_ms = 1e30f;
-    DevMem tile_mem;
+    // row tiles (kb_tile) and the tiles of the sectors it does not take (kb_apply)
+    struct Sched {
+        DevMem row, rest;
+        unsigned nrow = 0, nrest = 0;
+        size_t lrow = 0, lrest = 0;
+    };
+    std::unique_ptr<Sched> best;
     hipEvent_t ev0, ev1;
     ED_HIP(hipEventCreate(&ev0));
     ED_HIP(hipEventCreate(&ev1));
     auto kern0 = kb_apply<TX, TX, 0>;
+    auto kern1 = kb_tile<TX>;
     (void)hipFuncSetAttribute((const void *)kern0, hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
+    (void)hipFuncSetAttribute((const void *)kern1, hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
     (void)hipGetLastError();
+    auto apply_step = [&](const Sched &q, hipStream_t cs) {
+        if (q.nrow)
+            kern1<<<q.nrow, kBBS, q.lrow, cs>>>(d_sec, q.row.template as<ATile>(), st.jcur, st.active);
+        if (q.nrest)
+            kern0<<<q.nrest, kBBS, q.lrest, cs>>>(d_sec, q.rest.template as<ATile>(), st.jcur, st.active, 0, nullptr);
+    };
     for (int64_t tsz : cands) {
-        size_t lds = 0;
-        std::vector<ATile> tl = make_tiles(B, tsz, B.elem, &lds);
-        tile_mem.alloc(tl.size() * sizeof(ATile));
-        ED_HIP(hipMemcpyAsync(tile_mem.p, tl.data(), tl.size() * sizeof(ATile), hipMemcpyHostToDevice, s));
-        kern0<<<(unsigned)tl.size(), kBBS, lds, s>>>(d_sec, tile_mem.as<ATile>(), st.jcur, st.active, 0, nullptr);
+        auto q = std::make_unique<Sched>();
+        const std::vector<ATile> tr = make_row_tiles(B, tsz, B.elem, &q->lrow);
+        const std::vector<ATile> ts = make_tiles(B, tsz, B.elem, true, &q->lrest);
+        q->nrow = (unsigned)tr.size();
+        q->nrest = (unsigned)ts.size();
+        q->row.alloc(tr.size() * sizeof(ATile));
+        q->rest.alloc(ts.size() * sizeof(ATile));
+        if (q->nrow) ED_HIP(hipMemcpyAsync(q->row.p, tr.data(), tr.size() * sizeof(ATile), hipMemcpyHostToDevice, s));
+        if (q->nrest) ED_HIP(hipMemcpyAsync(q->rest.p, ts.data(), ts.size() * sizeof(ATile), hipMemcpyHostToDevice, s));
+        apply_step(*q, s);
         ED_HIP(hipEventRecord(ev0, s));
-        for (int r = 0; r < 3; ++r)
-            kern0<<<(unsigned)tl.size(), kBBS, lds, s>>>(d_sec, tile_mem.as<ATile>(), st.jcur, st.active, 0, nullptr);
+        for (int r = 0; r < 3; ++r) apply_step(*q, s);
         ED_HIP(hipEventRecord(ev1, s));
         ED_LAUNCH_CHECK();
         ED_HIP(hipEventSynchronize(ev1));
@@ -950,14 +1224,16 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
         ED_HIP(hipEventElapsedTime(&ms, ev0, ev1));
         if (ms < best_ms) {
             best_ms = ms;
-            best_tiles = tl;
-            best_lds = lds;
+            best = std::move(q);
             best_tile_size = tsz;
         }
     }
     (void)hipEventDestroy(ev0);
     (void)hipEventDestroy(ev1);
+    // tiles of the final Rayleigh quotients, every sector
     DevMem tiles;
+    size_t best_lds = 0;
+    const std::vector<ATile> best_tiles = make_tiles(B, 2048, B.elem, false, &best_lds);
     tiles.alloc(best_tiles.size() * sizeof(ATile));
     ED_HIP(hipMemcpyAsync(tiles.p, best_tiles.data(), best_tiles.size() * sizeof(ATile), hipMemcpyHostToDevice, s));
     const unsigned nt = (unsigned)best_tiles.size();
@@ -967,7 +1243,7 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     const int passes = o.reorth == 2 ? 2 : 1;
     const unsigned prow = (unsigned)(o.reorth == 3 ? 2 * (m + 1) : m + 1);
     auto record_step = [&](hipStream_t cs) {
-        kb_apply<TX, TX, 0><<<nt, kBBS, best_lds, cs>>>(d_sec, tiles.as<ATile>(), st.jcur, st.active, 0, nullptr);
+        apply_step(*best, cs);
         for (int ps = 0; ps < passes; ++ps) {
             if (o.reorth == 3) kb_dots_v4<TX, 8, true><<<nch_u, kBBS, 0, cs>>>(d_sec, d_ch, st, o.reorth, part);
             else kb_dots_v4<TX, 8, false><<<nch_u, kBBS, 0, cs>>>(d_sec, d_ch, st, o.reorth, part);

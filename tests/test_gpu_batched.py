@@ -154,3 +154,31 @@ def test_batched_implicit_restart_fp64_matches_explicit():
     assert any(i["restarts"] > 0 for i in i1)
     for a, b in zip(E1, E2):
         assert abs(a - b) <= 1e-10 * max(1.0, abs(b))
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("tile", [64, 4096, 16384])
+@pytest.mark.parametrize("name", ["generic6", "hub3x2", "kan6"])
+def test_batched_row_tiles(name, tile, prec, monkeypatch):
+    """Row tiles of one, several and all rows of a sector (rows of 1 to 20 columns:
+    every remainder of the four-column items) against dense spectra: per-site U
+    and a general cross term, connected and grouped move graphs; the sectors
+    without down hops take the other apply kernel."""
+    import oracle as orc
+    from gpu_common import generic_model, generic_terms
+    ed = gpu_ed()
+    monkeypatch.setenv("ED_BATCH_TILE", str(tile))
+    if name == "generic6":
+        p = generic_model(6, 31)
+        terms = generic_terms(p)
+    else:
+        phys = wl.hubbard(3, 2, 1.0, 4.0) if name == "hub3x2" else wl.kanamori(3, 1, 2.3, 0.4, seed=6)
+        p, terms = models.params_from_model(phys), orc.terms_from_model(phys)
+    secs = [(a, b) for a in range(7) for b in range(7)]
+    hs = [ed.Hamiltonian(p, ed.Basis(6, *s), prec) for s in secs]
+    E, info = ed.lanczos_ground_batched(hs, ed.options(tol=1e-10 if prec == 0 else 1e-7, max_basis=60, reorth=2,
+                                                       max_iter=2000), seed=3)
+    for e, i, (a, b) in zip(E, info, secs):
+        ref = np.linalg.eigvalsh(orc.Sector(6, a, b, terms).dense())[0]
+        assert i["converged"] == 1, (a, b)
+        assert abs(e - ref) <= (1e-10 if prec == 0 else 1e-6) * max(1.0, abs(ref)), (name, a, b, e, ref)
