@@ -23,7 +23,6 @@
 #include <cmath>
 #include <cstdlib>
 #include <memory>
-#include <thread>
 #include <vector>
 
 #include "ed_internal.h"
@@ -76,12 +75,15 @@ struct RChunk {
 struct BState {
     double *sig2, *gamma, *alpha, *beta, *tri, *raw, *gram, *coef, *a2b2;
     double *theta, *resid;
-    int *active;  // 0 done, 1 running, 2 basis full (waiting for a restart)
+    int *active;  // 0 done, 1 running, 2 basis full (restarts at the end of the step)
     int *jcur;    // step index of the running cycle
     int *nsteps;  // size of the tridiagonal matrix behind theta / tri
     int *iters;   // steps taken, all cycles
     int *rnin, *rnout, *rmode;  // restart request: inputs, outputs, 1 explicit 2 implicit 3 final
     double *nvsum;              // stored vectors projected against, summed over all steps
+    int *nrest;                 // restarts
+    double *rvec;               // vectors read and written by them
+    int *ev;                    // [0] steps in which a sector restarted, [1] the last of them, [2] steps
 };
 
 struct BDims {
@@ -363,7 +365,8 @@ __global__ __launch_bounds__(kBBS, sizeof(TX) == 4 ? 6 : 4) void kb_tile(const B
         }
         // 1 (x) H_dn
         {
-            const int32_t eb = S.dn_ell4_off[q >> 6], kk = (S.dn_ell4_off[(q >> 6) + 1] - eb) >> 6;
+            const int32_t eb = S.namp ? S.dn_ell4_off[q >> 6] : 0;
+            const int32_t kk = S.namp ? (S.dn_ell4_off[(q >> 6) + 1] - eb) >> 6 : 0;
             const uint4 *ep = S.dn_ell4 + eb + (q & 63u);
 #pragma unroll 2
             for (int32_t h = 0; h < kk; ++h) {
@@ -507,24 +510,17 @@ __global__ __launch_bounds__(kBBS) void kb_dots_v4(const BSec<TX, TX> *secs, con
 // Row sums of the chunk partials, one wave per (row, sector) in a fixed order:
 // raw[s * rs + r] = sum_c part[pbase + r * nch + c].  Rows: what: 0 = the
 // projection rows of the running sectors (nv, or 2 nv with the Gram read),
-// 1 = row 0 of the running sectors (norm), 2 = row 0 of the sectors with a
-// restart request.
+// 1 = row 0 of the running sectors (norm).
 template <typename TX>
 __global__ __launch_bounds__(64) void kb_rowsum(const BSec<TX, TX> *secs, BState st, BDims dm, int what,
                                                 const double *part) {
     const int r = blockIdx.x, s = blockIdx.y;
-    int rows;
-    if (what == 2) {
-        if (st.rnout[s] <= 0) return;
-        rows = 1;
-    } else {
-        if (st.active[s] != 1) return;
-        if (what == 1) rows = 1;
-        else {
-            const int j = st.jcur[s];
-            const int nv = j + 1 - win_begin(dm.reorth, j);
-            rows = dm.reorth == 3 ? 2 * nv : nv;
-        }
+    if (st.active[s] != 1) return;
+    int rows = 1;
+    if (what == 0) {
+        const int j = st.jcur[s];
+        const int nv = j + 1 - win_begin(dm.reorth, j);
+        rows = dm.reorth == 3 ? 2 * nv : nv;
     }
     if (r >= rows) return;
     const BSec<TX, TX> &S = secs[s];
@@ -761,22 +757,167 @@ __global__ __launch_bounds__(kBBS) void kb_restart_v4(const BSec<TX, TX> *secs, 
     if (threadIdx.x == 0) part[S.pbase + c.c] = sm;
 }
 
+// Restart plan of every sector whose basis is full (active = 2), one workgroup
+// per sector, in the step itself, so a sector restarts without waiting for the
+// host.  Implicit (exact-shift Lanczos restart, as ir_plan): the m Ritz values by
+// bisection, one per thread; for each of the m - keep largest a shifted QR step
+// T <- R Q + mu I of the tridiagonal matrix by one thread (the rotations in LDS),
+// which every thread then applies to its rows of Q; the coefficients of the kept
+// vectors and the new residual.  If that does not apply (non-finite data, the
+// lowest Ritz value lost) or keep = 0: from the Ritz vector.  Bound by the latency
+// of the rotations' chain, about 40 us for m = 20, keep = 8; the same plans on the
+// host (16 threads, up to a hundred waiting sectors, their states copied there and
+// back) left the GPU idle for 0.1 ms per step on average.  Q in LDS for m <=
+// kPlanLds, else in qg.
+static constexpr int kPlanLds = 80;
+__global__ __launch_bounds__(256) void kb_plan(BState st, BDims dm, int keep, double *qg) {
+    const int s = blockIdx.x;
+    if (st.active[s] != 2) return;
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    __shared__ double a[257], b[257], b2[257], sg[258], ev[257], cs[257], sn[257];
+    __shared__ double sh[4], t0_s;
+    const int t = threadIdx.x, m = dm.m, ns = st.nsteps[s];
+    const double *alpha = st.alpha + (int64_t)s * dm.ms, *beta = st.beta + (int64_t)s * dm.ms;
+    const double *sig2 = st.sig2 + (int64_t)s * dm.ms;
+    double *C = st.coef + (int64_t)s * dm.mc;
+    bool ok = keep > 0 && keep < m && ns == m;
+    if (ok) {  // uniform: m <= 256 with keep > 0
+        int bad = 0;
+        for (int i = t; i <= m; i += 256) {
+            sg[i] = sig2[i];
+            if (!(sg[i] > 0.0)) bad = 1;
+            if (i == m) break;
+            a[i] = alpha[i];
+            b[i] = beta[i];
+            if (!isfinite(a[i]) || !isfinite(b[i])) bad = 1;
+        }
+        ok = __syncthreads_or(bad) == 0;
+    }
+    if (ok) {
+        double lo = 1e300, hi = -1e300;
+        for (int i = t; i < m; i += 256) {
+            const double r = (i > 0 ? fabs(b[i - 1]) : 0.0) + (i < m - 1 ? fabs(b[i]) : 0.0);
+            lo = fmin(lo, a[i] - r);
+            hi = fmax(hi, a[i] + r);
+        }
+        lo = wg_reduce(lo, 0, sh);
+        hi = wg_reduce(hi, 1, sh);
+        const double nrm = fmax(fabs(lo), fabs(hi));
+        const double sc = nrm > 0.0 ? ldexp(1.0, -ilogb(nrm)) : 1.0;  // exact
+        const double blast = b[m - 1];
+        lo *= sc;
+        hi *= sc;
+        __syncthreads();
+        for (int i = t; i < m; i += 256) {
+            a[i] *= sc;
+            b[i] = i < m - 1 ? b[i] * sc : 0.0;
+            b2[i] = b[i] * b[i];
+        }
+        __syncthreads();
+        auto bisect = [&](int n, int idx) {
+            double l = lo, h = hi;
+            for (int it = 0; it < 120; ++it) {
+                const double mid = 0.5 * (l + h);
+                if (mid <= l || mid >= h) break;
+                if (sturm_count(a, b2, n, mid) > idx) h = mid;
+                else l = mid;
+            }
+            return 0.5 * (l + h);
+        };
+        for (int i = t; i < m; i += 256) ev[i] = bisect(m, i);
+        double *Q = m <= kPlanLds ? reinterpret_cast<double *>(smem_raw) : qg + (int64_t)s * m * m;  // [col][row]
+        for (int i = t; i < m * m; i += 256) Q[i] = i % (m + 1) == 0 ? 1.0 : 0.0;
+        __syncthreads();
+        for (int e = keep; e < m; ++e) {
+            if (t == 0) {
+                const double mu = ev[e];
+                double x = a[0] - mu, u = b[0], cp = 1.0, sp = 0.0;
+                for (int i = 0; i < m - 1; ++i) {
+                    const double z = b[i], r = sqrt(fma(x, x, z * z));
+                    const double ri = r > 0.0 ? 1.0 / r : 0.0;
+                    const double c = r > 0.0 ? x * ri : 1.0, sv = z * ri, an = a[i + 1] - mu;
+                    if (i > 0) b[i - 1] = sp * r;
+                    a[i] = cp * (c * r) + sv * fma(c, u, sv * an) + mu;
+                    x = fma(c, an, -(sv * u));
+                    u = i + 1 < m - 1 ? c * b[i + 1] : 0.0;
+                    cp = c;
+                    sp = sv;
+                    cs[i] = c;
+                    sn[i] = sv;
+                }
+                b[m - 2] = sp * x;
+                a[m - 1] = cp * x + mu;
+            }
+            __syncthreads();
+            for (int k = t; k < m; k += 256) {
+                double q = Q[k];
+                for (int i = 0; i < m - 1; ++i) {
+                    const double p = Q[(i + 1) * m + k];
+                    Q[i * m + k] = cs[i] * q + sn[i] * p;
+                    q = cs[i] * p - sn[i] * q;
+                }
+                Q[(m - 1) * m + k] = q;
+            }
+            __syncthreads();
+        }
+        for (int i = t; i < keep; i += 256) b2[i] = i < keep - 1 ? b[i] * b[i] : 0.0;
+        __syncthreads();
+        if (t == 0) t0_s = bisect(keep, 0);
+        __syncthreads();
+        ok = fabs(t0_s - ev[0]) <= 1e-8 * fmax(sc, fabs(ev[0]));
+        if (ok) {
+            const int nout = keep + 1;
+            const double tk = b[keep - 1] / sc;
+            for (int i = t; i < m * nout; i += 256) {
+                const int l = i / nout, o = i - l * nout;
+                C[i] = Q[o * m + l] * sqrt(sg[l]) * (o == keep ? tk : 1.0);
+            }
+            for (int o = t; o < nout; o += 256)
+                C[(int64_t)m * nout + o] = o == keep ? blast * sqrt(sg[m]) * Q[(keep - 1) * m + m - 1] : 0.0;
+            double *ab = st.a2b2 + (int64_t)s * 34;
+            for (int i = t; i < keep; i += 256) {
+                ab[i] = a[i] / sc;
+                ab[17 + i] = i + 1 < keep ? b[i] / sc : 0.0;
+            }
+        }
+    }
+    if (!ok)
+        for (int l = t; l < ns; l += 256) C[l] = st.tri[(int64_t)s * dm.mt + 3 + l] * sqrt(sig2[l]);
+    if (t == 0) {
+        const int nin = ok ? m + 1 : ns, nout = ok ? keep + 1 : 1;
+        st.rnin[s] = nin;
+        st.rnout[s] = nout;
+        st.rmode[s] = ok ? 2 : 1;
+        st.nrest[s] += 1;
+        st.rvec[s] += (double)(nin + nout);
+        const int step = st.ev[2];
+        if (atomicExch(&st.ev[1], step + 1) != step + 1) atomicAdd(&st.ev[0], 1);
+    }
+}
+
 // After the combination, per sector with a request: reset the recurrence.
 // Explicit (from the Ritz vector, now S_0): sigma_0^2 = 1 / ||S_0||^2, step 0.
 // Implicit (k kept orthonormal vectors, residual in S_k): the new leading
 // tridiagonal block from a2b2, beta_{k-1} = ||f||, the Gram block of the kept
 // vectors = I, step k; when ||f|| vanishes the kept vectors span an invariant
-// subspace and the sector finishes on T_k.  Every request is cleared.
-__global__ __launch_bounds__(256) void kb_restart_fin(BState st, BDims dm) {
+// subspace and the sector finishes on T_k.  The Ritz vector's coefficients are
+// those on the new basis from here on.  Every request is cleared.
+template <typename TX>
+__global__ __launch_bounds__(256) void kb_restart_fin(const BSec<TX, TX> *secs, BState st, BDims dm,
+                                                      const double *part) {
     const int s = blockIdx.x;
     const int mode = st.rmode[s];
+    if (s == 0 && threadIdx.x == 0) st.ev[2] += 1;
     if (st.rnout[s] <= 0 || mode == 3) {
         if (threadIdx.x == 0) st.rnout[s] = 0;
         return;
     }
     __shared__ int brk_s;
+    __shared__ double sh[4];
     const int k = st.rnout[s] - 1;  // implicit: kept vectors
-    const double n2 = st.raw[(int64_t)s * dm.rs];
+    double n2 = 0.0;
+    for (int c = threadIdx.x; c < secs[s].nch; c += 256) n2 += part[secs[s].pbase + c];
+    n2 = wg_reduce(n2, 2, sh);
     double *alpha = st.alpha + (int64_t)s * dm.ms, *beta = st.beta + (int64_t)s * dm.ms;
     double *sig2 = st.sig2 + (int64_t)s * dm.ms;
     const double *a2 = st.a2b2 + (int64_t)s * 2 * 17, *b2 = a2 + 17;
@@ -808,18 +949,20 @@ __global__ __launch_bounds__(256) void kb_restart_fin(BState st, BDims dm) {
     if (mode == 1) {
         if (threadIdx.x == 0) {
             sig2[0] = n2 > 0.0 ? 1.0 / n2 : 0.0;
+            st.tri[(int64_t)s * dm.mt + 3] = 1.0;
+            st.nsteps[s] = 1;
             st.jcur[s] = 0;
             st.active[s] = brk_s ? 0 : 1;
             st.rnout[s] = 0;
         }
         return;
     }
+    k_tridiag_lowest_body(alpha, beta, k, st.tri + (int64_t)s * dm.mt);
+    if (threadIdx.x == 0) st.nsteps[s] = k;
     if (brk_s) {  // finish on the kept block
-        k_tridiag_lowest_body(alpha, beta, k, st.tri + (int64_t)s * dm.mt);
         if (threadIdx.x == 0) {
             st.theta[s] = st.tri[(int64_t)s * dm.mt];
             st.resid[s] = 0.0;
-            st.nsteps[s] = k;
             st.active[s] = 0;
             st.rnout[s] = 0;
         }
@@ -950,6 +1093,9 @@ static size_t batch_layout(Batch &B, char *base, void **secs32, void **secs64, v
     t.rnin = (int *)c.take(S * 4);
     t.rnout = (int *)c.take(S * 4);
     t.rmode = (int *)c.take(S * 4);
+    t.nrest = (int *)c.take(S * 4);
+    t.rvec = (double *)c.take(S * 8);
+    t.ev = (int *)c.take(3 * 4);
     if (st) *st = t;
     double *r = (double *)c.take(S * 16 + 64);
     if (rq) *rq = r;
@@ -994,7 +1140,7 @@ static BSec<TX, TA> make_bsec(const ed_ham_s *h, TX *base, int nch, int64_t pbas
     b.dn_ell4_off = Dn.ell4_off.as<int32_t>();
     b.dn_ell4 = Dn.ell4.as<uint4>();
     b.amp_tab = (const TA *)(dbl ? Dn.amp64.p : Dn.amp32.p);
-    b.namp = Dn.namp;
+    b.namp = Dn.pk_ok ? Dn.namp : 0;  // 0: no down hops (row_tile_fits)
     b.um = (U.max_hops + 3) & ~3;
     b.xm = h->nx ? h->xl_max : 0;
     b.nch = nch;
@@ -1006,14 +1152,16 @@ static BSec<TX, TA> make_bsec(const ed_ham_s *h, TX *base, int nch, int64_t pbas
 static size_t row_tile_lds(const ed_ham_s *h, int nr, size_t elem) {
     const int R = 16 / (int)elem;
     const size_t um = (size_t)((h->sp[0].max_hops + 3) & ~3), xm = h->nx ? (size_t)h->xl_max : 0;
-    return (size_t)((nr + R - 1) / R) * R * (size_t)h->ddn * elem + (size_t)h->sp[1].namp * elem +
+    return (size_t)((nr + R - 1) / R) * R * (size_t)h->ddn * elem +
+           (h->sp[1].pk_ok ? (size_t)h->sp[1].namp * elem : 0) +
            (size_t)nr * (um * (elem + 4) + xm * (elem + 8));
 }
 static constexpr size_t kRowTileLds = 60 * 1024;
-// Sectors kb_tile takes: packed down hops, the cross table in LDS, one group of
-// rows in LDS.  The others (no down hops at all, very long rows) go to kb_apply.
+// Sectors kb_tile takes: down hops packed (or none), the cross table and one group
+// of rows in LDS.  The others (thousands of distinct amplitudes, rows of more than
+// about 3800 FP32 or 1900 FP64 states) go to kb_apply.
 static bool row_tile_fits(const ed_ham_s *h, size_t elem) {
-    return h->sp[1].pk_ok && h->koff <= 4 &&
+    return (h->sp[1].pk_ok || h->sp[1].nnz == 0) && h->koff <= 4 &&
            row_tile_lds(h, (int)std::min<int64_t>(16 / (int64_t)elem, h->dup), elem) <= kRowTileLds;
 }
 
@@ -1115,9 +1263,12 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
         for (double *p : {st.sig2, st.gamma, st.alpha, st.beta})
             ED_HIP(hipMemcpyAsync(p, z0.data(), S * dm.ms * 8, hipMemcpyHostToDevice, s));
         ED_HIP(hipMemcpyAsync(st.tri, z0.data(), S * dm.mt * 8, hipMemcpyHostToDevice, s));
-        for (double *p : {st.theta, st.resid, st.nvsum}) ED_HIP(hipMemcpyAsync(p, z0.data(), S * 8, hipMemcpyHostToDevice, s));
-        for (int *p : {st.active, st.jcur, st.nsteps, st.iters, st.rnin, st.rnout, st.rmode})
+        for (double *p : {st.theta, st.resid, st.nvsum, st.rvec}) ED_HIP(hipMemcpyAsync(p, z0.data(), S * 8, hipMemcpyHostToDevice, s));
+        for (int *p : {st.active, st.jcur, st.nsteps, st.iters, st.rnin, st.rnout, st.rmode, st.nrest})
             ED_HIP(hipMemcpyAsync(p, i0.data(), S * 4, hipMemcpyHostToDevice, s));
+        const int e0[3] = {0, 0, 0};
+        ED_HIP(hipMemcpyAsync(st.ev, e0, sizeof(e0), hipMemcpyHostToDevice, s));
+        ED_HIP(hipStreamSynchronize(s));
     }
     // start vectors -> slot 0
     for (int i = 0; i < nsec; ++i) {
@@ -1130,26 +1281,27 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     }
     ED_LAUNCH_CHECK();
 
-    // ---- restart requests: host-side coefficients, one batched combination
-    std::vector<double> h_al(S * dm.ms), h_be(S * dm.ms), h_sg(S * dm.ms), h_tri(S * dm.mt);
-    std::vector<double> h_coef(S * dm.mc, 0.0), h_a2b2(S * 34, 0.0);
+    // ---- the first and the last combination are requested here (S_0 as given, the
+    // final Ritz vectors); the restarts in between are planned on the device
+    std::vector<double> h_sg(S * dm.ms), h_tri(S * dm.mt), h_coef(S * dm.mc, 0.0);
     std::vector<int> h_nsteps(S), h_rnin(S), h_rnout(S), h_rmode(S);
     double restart_bytes = 0.0;
-    auto launch_restart = [&](int maxout) {
+    auto combine = [&](int maxout, hipStream_t cs) {
+        if (maxout <= 1) kb_restart_v4<TX, 1><<<nch_u, kBBS, 0, cs>>>(d_sec, d_ch, st, dm, part);
+        else if (maxout <= 3) kb_restart_v4<TX, 3><<<nch_u, kBBS, 0, cs>>>(d_sec, d_ch, st, dm, part);
+        else if (maxout <= 5) kb_restart_v4<TX, 5><<<nch_u, kBBS, 0, cs>>>(d_sec, d_ch, st, dm, part);
+        else if (maxout <= 9) kb_restart_v4<TX, 9><<<nch_u, kBBS, 0, cs>>>(d_sec, d_ch, st, dm, part);
+        else kb_restart_v4<TX, 17><<<nch_u, kBBS, 0, cs>>>(d_sec, d_ch, st, dm, part);
+        kb_restart_fin<TX><<<nsec, 256, 0, cs>>>(d_sec, st, dm, part);
+    };
+    auto launch_request = [&]() {
         for (int q = 0; q < nsec; ++q)
             if (h_rnout[q] > 0) restart_bytes += (double)(h_rnin[q] + h_rnout[q]) * (double)B.D[q] * (double)B.elem;
         ED_HIP(hipMemcpyAsync(st.coef, h_coef.data(), h_coef.size() * 8, hipMemcpyHostToDevice, s));
-        ED_HIP(hipMemcpyAsync(st.a2b2, h_a2b2.data(), h_a2b2.size() * 8, hipMemcpyHostToDevice, s));
         ED_HIP(hipMemcpyAsync(st.rnin, h_rnin.data(), S * 4, hipMemcpyHostToDevice, s));
         ED_HIP(hipMemcpyAsync(st.rnout, h_rnout.data(), S * 4, hipMemcpyHostToDevice, s));
         ED_HIP(hipMemcpyAsync(st.rmode, h_rmode.data(), S * 4, hipMemcpyHostToDevice, s));
-        if (maxout <= 1) kb_restart_v4<TX, 1><<<nch_u, kBBS, 0, s>>>(d_sec, d_ch, st, dm, part);
-        else if (maxout <= 3) kb_restart_v4<TX, 3><<<nch_u, kBBS, 0, s>>>(d_sec, d_ch, st, dm, part);
-        else if (maxout <= 5) kb_restart_v4<TX, 5><<<nch_u, kBBS, 0, s>>>(d_sec, d_ch, st, dm, part);
-        else if (maxout <= 9) kb_restart_v4<TX, 9><<<nch_u, kBBS, 0, s>>>(d_sec, d_ch, st, dm, part);
-        else kb_restart_v4<TX, 17><<<nch_u, kBBS, 0, s>>>(d_sec, d_ch, st, dm, part);
-        kb_rowsum<TX><<<dim3(1, (unsigned)nsec), 64, 0, s>>>(d_sec, st, dm, 2, part);
-        kb_restart_fin<<<nsec, 256, 0, s>>>(st, dm);
+        combine(1, s);
         ED_LAUNCH_CHECK();
     };
     // explicit (or final) request for sector q: S_0 <- sum_l s_l sigma_l S_l
@@ -1163,8 +1315,6 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
         h_rmode[q] = mode;
     };
     auto fetch_state = [&]() {
-        ED_HIP(hipMemcpyAsync(h_al.data(), st.alpha, S * dm.ms * 8, hipMemcpyDeviceToHost, s));
-        ED_HIP(hipMemcpyAsync(h_be.data(), st.beta, S * dm.ms * 8, hipMemcpyDeviceToHost, s));
         ED_HIP(hipMemcpyAsync(h_sg.data(), st.sig2, S * dm.ms * 8, hipMemcpyDeviceToHost, s));
         ED_HIP(hipMemcpyAsync(h_tri.data(), st.tri, S * dm.mt * 8, hipMemcpyDeviceToHost, s));
         ED_HIP(hipMemcpyAsync(h_nsteps.data(), st.nsteps, S * 4, hipMemcpyDeviceToHost, s));
@@ -1175,11 +1325,11 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     std::fill(h_rnout.begin(), h_rnout.end(), 1);
     std::fill(h_rmode.begin(), h_rmode.end(), 1);
     for (int q = 0; q < nsec; ++q) h_coef[(size_t)q * dm.mc] = 1.0;
-    launch_restart(1);
+    launch_request();
     ED_HIP(hipStreamSynchronize(s));
 
     // ---- tile schedule: time a few tile sizes on slot 0 -> slot 1 (every sector at step 0)
-    std::vector<int64_t> cands = {2048, 4096, 8192, 16384};
+    std::vector<int64_t> cands = {4096, 8192};
     if (const char *env = std::getenv("ED_BATCH_TILE")) cands = {std::max<int64_t>(64, std::atoll(env))};
     int64_t best_tile_size = 0;
     float best_ms = 1e30f;
@@ -1242,6 +1392,9 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     // ---- one step of every running sector, captured once
     const int passes = o.reorth == 2 ? 2 : 1;
     const unsigned prow = (unsigned)(o.reorth == 3 ? 2 * (m + 1) : m + 1);
+    DevMem plan_q;
+    if (o.keep > 0 && m > kPlanLds) plan_q.alloc(S * (size_t)m * (size_t)m * 8);
+    const size_t plan_lds = o.keep > 0 && m <= kPlanLds ? (size_t)m * (size_t)m * 8 : 0;
     auto record_step = [&](hipStream_t cs) {
         apply_step(*best, cs);
         for (int ps = 0; ps < passes; ++ps) {
@@ -1253,6 +1406,9 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
         }
         kb_rowsum<TX><<<dim3(1, (unsigned)nsec), 64, 0, cs>>>(d_sec, st, dm, 1, part);
         kb_tridiag<<<nsec, 256, 0, cs>>>(st, dm, o.tol);
+        // sectors whose basis is full restart
+        kb_plan<<<nsec, 256, plan_lds, cs>>>(st, dm, o.keep, plan_q.as<double>());
+        combine(o.keep > 0 ? o.keep + 1 : 1, cs);
     };
     hipStream_t cs;
     ED_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
@@ -1264,7 +1420,7 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     ED_HIP(hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0));
 
     std::vector<int> act(S), restarts(S, 0);
-    int64_t launches = 0, events = 0;
+    int64_t launches = 0;
     const int every = std::max(1, o.check_every);
     while (launches < o.max_iter) {
         const int n = (int)std::min<int64_t>(every, o.max_iter - launches);
@@ -1272,69 +1428,7 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
         launches += n;
         ED_HIP(hipMemcpyAsync(act.data(), st.active, S * 4, hipMemcpyDeviceToHost, s));
         ED_HIP(hipStreamSynchronize(s));
-        int on = 0, pend = 0;
-        for (int q = 0; q < nsec; ++q) {
-            on += act[q] == 1;
-            pend += act[q] == 2;
-        }
-        if (on == 0 && pend == 0) break;
-        if (launches >= o.max_iter || pend == 0) continue;
-        // restart every sector whose basis is full; the shift plans of the
-        // waiting sectors are independent host computations, spread over threads
-        fetch_state();
-        std::fill(h_rnout.begin(), h_rnout.end(), 0);
-        std::vector<int> pending;
-        for (int q = 0; q < nsec; ++q)
-            if (act[q] == 2) {
-                ++restarts[q];
-                pending.push_back(q);
-            }
-        std::vector<char> implicit(pending.size(), 0);
-        auto plan_range = [&](size_t b, size_t e) {
-            std::vector<double> Cq, a2q, b2q, evq;
-            for (size_t t = b; t < e; ++t) {
-                const int q = pending[t];
-                if (!(o.keep > 0 && o.keep < m && h_nsteps[q] == m)) continue;
-                std::vector<double> al(h_al.begin() + (size_t)q * dm.ms, h_al.begin() + (size_t)q * dm.ms + m);
-                std::vector<double> be(h_be.begin() + (size_t)q * dm.ms, h_be.begin() + (size_t)q * dm.ms + m);
-                std::vector<double> sg(h_sg.begin() + (size_t)q * dm.ms, h_sg.begin() + (size_t)q * dm.ms + m + 1);
-                if (!ir_plan(al, be, sg, m, o.keep, Cq, a2q, b2q, evq)) continue;
-                std::copy(Cq.begin(), Cq.end(), h_coef.begin() + (size_t)q * dm.mc);
-                double *ab = h_a2b2.data() + (size_t)q * 34;
-                for (int i = 0; i < o.keep; ++i) {
-                    ab[i] = a2q[i];
-                    ab[17 + i] = i + 1 < o.keep ? b2q[i] : 0.0;
-                }
-                implicit[t] = 1;
-            }
-        };
-        const size_t nth = std::min<size_t>(std::min<size_t>(pending.size() / 4 + 1, 16),
-                                            std::max(1u, std::thread::hardware_concurrency()));
-        if (nth <= 1) {
-            plan_range(0, pending.size());
-        } else {
-            std::vector<std::thread> pool;
-            const size_t per = (pending.size() + nth - 1) / nth;
-            for (size_t k = 0; k < nth; ++k) {
-                const size_t b = k * per, e = std::min(pending.size(), b + per);
-                if (b < e) pool.emplace_back(plan_range, b, e);
-            }
-            for (auto &t : pool) t.join();
-        }
-        int maxout = 1;
-        for (size_t t = 0; t < pending.size(); ++t) {
-            const int q = pending[t];
-            if (implicit[t]) {
-                h_rnin[q] = m + 1;
-                h_rnout[q] = o.keep + 1;
-                h_rmode[q] = 2;
-                maxout = std::max(maxout, o.keep + 1);
-            } else {
-                ritz_request(q, 1);
-            }
-        }
-        launch_restart(maxout);
-        ++events;
+        if (std::all_of(act.begin(), act.end(), [](int q) { return q == 0; })) break;
     }
     (void)hipGraphExecDestroy(gexec);
     (void)hipGraphDestroy(graph);
@@ -1345,10 +1439,14 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     fetch_state();
     std::fill(h_rnout.begin(), h_rnout.end(), 0);
     for (int q = 0; q < nsec; ++q) ritz_request(q, 3);
-    launch_restart(1);
+    launch_request();
     std::vector<double> theta(S), resid(S), rqv(2 * S, 0.0);
     std::vector<int> iters(S);
-    std::vector<double> nvsum(S);
+    std::vector<double> nvsum(S), rvec(S);
+    int evs[3] = {0, 0, 0};
+    ED_HIP(hipMemcpyAsync(restarts.data(), st.nrest, S * 4, hipMemcpyDeviceToHost, s));
+    ED_HIP(hipMemcpyAsync(rvec.data(), st.rvec, S * 8, hipMemcpyDeviceToHost, s));
+    ED_HIP(hipMemcpyAsync(evs, st.ev, sizeof(evs), hipMemcpyDeviceToHost, s));
     ED_HIP(hipMemcpyAsync(nvsum.data(), st.nvsum, S * 8, hipMemcpyDeviceToHost, s));
     ED_HIP(hipMemcpyAsync(theta.data(), st.theta, S * 8, hipMemcpyDeviceToHost, s));
     ED_HIP(hipMemcpyAsync(resid.data(), st.resid, S * 8, hipMemcpyDeviceToHost, s));
@@ -1383,7 +1481,7 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     for (int q = 0; q < nsec; ++q) {
         const double bq = (double)B.D[q] * (double)B.elem *
                           (2.0 * iters[q] + passes * (2.0 * nvsum[q] + 3.0 * iters[q]));
-        bytes += bq;
+        bytes += bq + rvec[q] * (double)B.D[q] * (double)B.elem;
         const bool conv = act[q] == 0;
         allconv &= conv;
         const double rqi = (o.refine && rqv[2 * q + 1] > 0.0) ? rqv[2 * q] / rqv[2 * q + 1] : theta[q];
@@ -1405,7 +1503,7 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     }
     g_last.tile = best_tiles.empty() ? 0 : best_tile_size;
     g_last.steps = launches;
-    g_last.restart_events = events;
+    g_last.restart_events = evs[0];
     g_last.bytes = bytes;
     return allconv ? ED_OK : ED_ENOCONV;
 }

@@ -162,8 +162,8 @@ def test_batched_implicit_restart_fp64_matches_explicit():
 def test_batched_row_tiles(name, tile, prec, monkeypatch):
     """Row tiles of one, several and all rows of a sector (rows of 1 to 20 columns:
     every remainder of the four-column items) against dense spectra: per-site U
-    and a general cross term, connected and grouped move graphs; the sectors
-    without down hops take the other apply kernel."""
+    and a general cross term, connected and grouped move graphs, sectors without
+    down hops."""
     import oracle as orc
     from gpu_common import generic_model, generic_terms
     ed = gpu_ed()
@@ -182,3 +182,26 @@ def test_batched_row_tiles(name, tile, prec, monkeypatch):
         ref = np.linalg.eigvalsh(orc.Sector(6, a, b, terms).dense())[0]
         assert i["converged"] == 1, (a, b)
         assert abs(e - ref) <= (1e-10 if prec == 0 else 1e-6) * max(1.0, abs(ref)), (name, a, b, e, ref)
+
+
+@pytest.mark.parametrize("basis,keep,reorth", [(8, 1, 2), (9, 4, 3), (14, 6, 3), (17, 16, 2), (80, 8, 3), (84, 8, 2),
+                                               (12, 0, 2)])
+def test_batched_restart_plans(basis, keep, reorth):
+    """Restarts planned on the device (Q in LDS up to 80 vectors, in memory
+    beyond; keep = 0: from the Ritz vector) against the oracle and, for the
+    long sectors, with restarts actually taken.  The 16 kept of 17 leave one
+    new step per restart."""
+    import oracle as orc
+    ed = gpu_ed()
+    phys = wl.kanamori(3, 2, 2.3, 0.4, seed=3)
+    p = models.params_from_model(phys)
+    secs = [(4, 5), (4, 4), (3, 5), (2, 2), (1, 4), (0, 3), (9, 9)]
+    hs = [ed.Hamiltonian(p, ed.Basis(9, *s), 0) for s in secs]
+    E, info = ed.lanczos_ground_batched(hs, ed.options(tol=1e-10, max_basis=basis, keep=keep, reorth=reorth,
+                                                       max_iter=6000), seed=7)
+    for e, i, s in zip(E, info, secs):
+        ref = orc.lowest_k(orc.sector_for(phys, *s), 1, tol=1e-13)[0]
+        assert i["converged"] == 1, (s, i)
+        assert abs(e - ref) <= 1e-10 * max(1.0, abs(ref)), (s, e, ref)
+    if basis <= 17:
+        assert info[0]["restarts"] > 0
