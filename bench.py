@@ -120,7 +120,7 @@ def schedule_kernels(name):
     """Kernels one apply launches under a schedule (by schedule-name prefix)."""
     for pre, k in (("gt2_", "k_gtile row pass + k_upt band pass"), ("gt_", "k_gtile"),
                    ("grp2_", "k_rt (grouped tiles) + k_upt band pass"), ("grp_", "k_rt (grouped tiles)"),
-                   ("rt_", "k_rt"), ("csx_", "k_cs row pass + k_upb band pass"),
+                   ("rtu_", "k_rt row pass + k_upt band pass"), ("rt_", "k_rt"), ("csx_", "k_cs row pass + k_upb band pass"),
                    ("rwpk_", "k_apply (packed table)"), ("rw_", "k_apply")):
         if name.startswith(pre):
             return k

@@ -498,7 +498,13 @@ __device__ __forceinline__ TA cross_term_l(const ApplyArgs<TX, TA> &a, const TA 
 // down components, so every down hop reads the staged tile; four-fermion
 // partners lie in other tiles and are read from memory; element offsets are
 // 32-bit, D < 2^32).
-template <typename TX, typename TA, int R, int BS, bool UPX, bool NTY, bool GRP = false>
+// WHOLE = true: rank order with the whole row as the one window, so every down
+// hop reads the staged tile.  Without it the read of a target outside the window
+// stays in the hop loop, and although no lane takes it, its load is issued with an
+// empty mask for each hop and column and the join waits for all loads in flight:
+// counters of the 4x4 Hubbard row (12,870 states, one window) showed 133 vector
+// memory instructions per 256 outputs where the data needs 26.
+template <typename TX, typename TA, int R, int BS, bool UPX, bool NTY, bool GRP = false, bool WHOLE = false>
 __global__ __launch_bounds__(BS) void k_rt(ApplyArgs<TX, TA> a) {
     using RVt = typename RV<TX, R>::t;
     using V = typename V4<TX>::t;
@@ -632,7 +638,7 @@ __global__ __launch_bounds__(BS) void k_rt(ApplyArgs<TX, TA> a) {
         for (int j = 0; j < 4; ++j) {
             const int64_t l = c + j - w0;
             const bool inw = FULL || (l >= 0 && l < wl);
-            RVt v = *reinterpret_cast<const RVt *>(xs + (inw ? l : 0) * R);
+            RVt v = *reinterpret_cast<const RVt *>(xs + (uint32_t)(inw ? l : 0) * R);
             if (!inw) v = (RVt)0;
 #pragma unroll
             for (int r = 0; r < R; ++r)
@@ -655,7 +661,11 @@ __global__ __launch_bounds__(BS) void k_rt(ApplyArgs<TX, TA> a) {
                     const int32_t t = (int32_t)(ev[j] & 0xFFFFFu);
                     const TA am = amps[ev[j] >> 20];
                     const int32_t l = t - w0;
-                    if constexpr (GRP) {  // the window holds the whole component
+                    if constexpr (WHOLE) {
+                        const RVt v = *reinterpret_cast<const RVt *>(xs + (uint32_t)t * R);
+#pragma unroll
+                        for (int r = 0; r < R; ++r) acc[r][j] += am * (TA)rv_get<TX, R>(v, r);
+                    } else if constexpr (GRP) {  // the window holds the whole component
                         // (a ragged chunk also computes columns outside the window,
                         // whose results are discarded: keep their reads in the tile)
                         const uint32_t lc = FULL ? (uint32_t)l : min((uint32_t)l, (uint32_t)(wl - 1));
@@ -980,74 +990,93 @@ __global__ __launch_bounds__(BS) void k_upb(ApplyArgs<TX, TA> a, int64_t band, i
     }
 }
 
-// Band pass over a work list (grouped schedules): y[u, band] += (H_up (x) 1) x
-// for the rows [u0, u0 + rows) of one item and one band of BAND columns.
-// In the grouped order an up component's rows are contiguous and every up hop
-// stays inside the component, so the items of one (component, band) tile run
-// on one XCD one after another and the tile's slice of x (rows x BAND) stays
-// in that XCD's L2 while its rows read it.  BS threads: BAND/4 column lanes x
-// BS/(BAND/4) row lanes, four consecutive columns per thread (16-byte
-// accesses at element alignment); y is read and written non-temporally.
+// Band pass over a work list: y[u, band] += (H_up (x) 1) x for the rows [u0, u0 +
+// rows) of one item and one band of BAND columns.  The items of a band (in the
+// grouped order, of an (up component, band) tile, which its up hops do not leave)
+// run on one XCD one after another, so the band's slice of x (rows x BAND) is read
+// from that XCD's L2 by all rows, where the one-pass kernels read a large
+// connected sector's partner rows from HBM again and again (4x4 Hubbard lattice:
+// 17 partners per row, 11 GB per FP32 product).  BS threads: BAND/4 column lanes x
+// BS/(BAND/4) row lanes, four consecutive columns per thread (16-byte accesses at
+// element alignment); the rows' hop lists are staged in LDS (read from memory per
+// hop they were two of three loads), eight FP32 or four FP64 partner loads in
+// flight; y is read and written non-temporally.  Bands of 128 columns: 0.99 ms at
+// the 4x4 Hubbard size (lists from memory: 1.22 ms), of 64 1.11, of 32 1.37, of 256
+// 1.08, of 512 1.45.  At most kUptRows rows per item and kUptHops hops per row.
+static constexpr int kUptRows = 32, kUptHops = 32;
 template <typename TX, typename TA, int BS, int BAND>
 __global__ __launch_bounds__(BS) void k_upt(ApplyArgs<TX, TA> a) {
     using V = typename V4<TX>::t;
-    constexpr int CL = BAND / 4, RL = BS / CL;
+    constexpr int CL = BAND / 4, RL = BS / CL, U = sizeof(TX) == 4 ? 8 : 4;
     static_assert(BS % CL == 0, "band must divide the workgroup");
+    __shared__ uint32_t s_t[kUptRows][kUptHops];
+    __shared__ TA s_a[kUptRows][kUptHops];
+    __shared__ int s_n[kUptRows];
     const int4 it = a.items[blockIdx.x];
-    const int64_t ddn = a.ddn;
+    const uint32_t ddn = (uint32_t)a.ddn;
+    const int nr = it.y;
+    if (nr <= 0) return;  // padding item: the whole workgroup leaves before the barrier
+    for (int k = threadIdx.x; k < nr * kUptHops; k += BS) {
+        const int r = k / kUptHops, i = k - r * kUptHops;
+        const int32_t hb = a.up_off[it.x + r], n = a.up_off[it.x + r + 1] - hb;
+        if (i == 0) s_n[r] = n;
+        if (i < n) {
+            s_t[r][i] = (uint32_t)a.up_tgt[hb + i] * ddn;
+            s_a[r][i] = a.up_sa[hb + i];
+        }
+    }
+    __syncthreads();
     const int cl = (int)threadIdx.x % CL, rl = (int)threadIdx.x / CL;
-    const int64_t c = (int64_t)it.z * BAND + 4 * cl;
-    if (it.y <= 0 || c >= ddn) return;  // no barriers in this kernel
+    const uint32_t c = (uint32_t)it.z * BAND + 4u * (uint32_t)cl;
+    if (c >= ddn) return;
     const bool full = c + 4 <= ddn;
-    for (int r = rl; r < it.y; r += RL) {
-        const int64_t u = (int64_t)it.x + r;
-        TX *yr = a.y + u * ddn;
+    for (int r = rl; r < nr; r += RL) {
+        TX *yr = a.y + ((uint32_t)it.x + (uint32_t)r) * ddn;
+        const int n = s_n[r];
         TA acc[4];
         if (full) {
             const V v = __builtin_nontemporal_load(reinterpret_cast<const V *>(yr + c));
             acc[0] = (TA)v.x; acc[1] = (TA)v.y; acc[2] = (TA)v.z; acc[3] = (TA)v.w;
-        } else {
+            int e = 0;
+            for (; e + U <= n; e += U) {
+                V w[U];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) acc[j] = c + j < ddn ? (TA)yr[c + j] : (TA)0;
-        }
-        const int32_t hb = a.up_off[u], he = a.up_off[u + 1];
-        int32_t e = hb;
-        if (full) {
-            for (; e + 4 <= he; e += 4) {
-                V v[4];
+                for (int i = 0; i < U; ++i) w[i] = ld4(a.x + (s_t[r][e + i] + c));
 #pragma unroll
-                for (int i = 0; i < 4; ++i) v[i] = ld4(a.x + (int64_t)a.up_tgt[e + i] * ddn + c);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const TA am = a.up_sa[e + i];
-                    acc[0] += am * (TA)v[i].x;
-                    acc[1] += am * (TA)v[i].y;
-                    acc[2] += am * (TA)v[i].z;
-                    acc[3] += am * (TA)v[i].w;
+                for (int i = 0; i < U; ++i) {
+                    const TA am = s_a[r][e + i];
+                    acc[0] += am * (TA)w[i].x;
+                    acc[1] += am * (TA)w[i].y;
+                    acc[2] += am * (TA)w[i].z;
+                    acc[3] += am * (TA)w[i].w;
                 }
             }
-            for (; e < he; ++e) {
-                const V v = ld4(a.x + (int64_t)a.up_tgt[e] * ddn + c);
-                const TA am = a.up_sa[e];
-                acc[0] += am * (TA)v.x;
-                acc[1] += am * (TA)v.y;
-                acc[2] += am * (TA)v.z;
-                acc[3] += am * (TA)v.w;
+            if (e < n) {  // the last ones, their loads in flight together
+                V w[U - 1];
+#pragma unroll
+                for (int i = 0; i < U - 1; ++i)
+                    if (e + i < n) w[i] = ld4(a.x + (s_t[r][e + i] + c));
+#pragma unroll
+                for (int i = 0; i < U - 1; ++i)
+                    if (e + i < n) {
+                        const TA am = s_a[r][e + i];
+                        acc[0] += am * (TA)w[i].x;
+                        acc[1] += am * (TA)w[i].y;
+                        acc[2] += am * (TA)w[i].z;
+                        acc[3] += am * (TA)w[i].w;
+                    }
             }
             V o;
             o.x = (TX)acc[0]; o.y = (TX)acc[1]; o.z = (TX)acc[2]; o.w = (TX)acc[3];
             st4<TX, true>(yr + c, o);
         } else {
-            for (; e < he; ++e) {
-                const TX *row = a.x + (int64_t)a.up_tgt[e] * ddn;
-                const TA am = a.up_sa[e];
 #pragma unroll
-                for (int j = 0; j < 4; ++j)
-                    if (c + j < ddn) acc[j] += am * (TA)row[c + j];
+            for (int j = 0; j < 4; ++j) {
+                if (c + j >= ddn) break;
+                TA t = (TA)yr[c + j];
+                for (int e = 0; e < n; ++e) t += s_a[r][e] * (TA)a.x[s_t[r][e] + c + j];
+                yr[c + j] = (TX)t;
             }
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (c + j < ddn) yr[c + j] = (TX)acc[j];
         }
     }
 }
@@ -1428,6 +1457,13 @@ static const Variant kVariants[] = {
     // 128 rows per XCD): for tiles larger than an XCD's L2 (N_s = 18: up to
     // 8000 rows x 32 KB)
     {12, 1, 512, 8192, "gt_r1_w8192_shared_c20"}, {12, 1, 512, 8192, "gt_r1_w8192_shared_c128"},
+    // transposed row tiles with 1024 threads: 51 KB of LDS (6435 FP64 states) leave
+    // room for two such workgroups, 32 waves per CU, against three of 512 threads
+    // (sector (6, 8) of the 15-site impurity, FP64: 530 -> 483 us)
+    {6, 1, 1024, 0, "rt_r1_b1024"},
+    // row pass (diagonal, 1 (x) H_dn, four-fermion terms) + band pass of H_up (x) 1
+    // over bands whose slice of x stays in an XCD's L2
+    {14, 2, 1024, 128, "rtu_r2_b1024_band128", 0, 32}, {14, 1, 1024, 128, "rtu_r1_b1024_band128", 0, 32},
 };
 static constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 static constexpr int64_t kDynBudget = 163840 - 8192;  // LDS left for the staged x block
@@ -1539,7 +1575,8 @@ static const int4 *items_cached(const ed_ham_s *h, int64_t key, int64_t *count) 
 static const int4 *items_for(ed_ham_s *h, int64_t key, const std::vector<int64_t> &cols, int rows,
                              int64_t *count) {
     if (const int4 *c = items_cached(h, key, count)) return c;
-    const std::vector<int32_t> &co = h->comp_off[0];
+    // rank order: all rows as one component
+    const std::vector<int32_t> co = h->grouped ? h->comp_off[0] : std::vector<int32_t>{0, (int32_t)h->dup};
     std::vector<int4> L;
     std::vector<double> cost;
     for (size_t A = 0; A + 1 < co.size(); ++A)
@@ -1924,7 +1961,7 @@ static void launch_rt(ed_ham_s *h, ApplyArgs<TX, TA> a, hipStream_t s, int64_t w
         allow_lds(kern);
         kern<<<(unsigned)nblk, BS, shm, s>>>(a);
     } else {
-        auto kern = k_rt<TX, TA, R, BS, UPX, true>;
+        auto kern = nwin == 1 ? k_rt<TX, TA, R, BS, UPX, true, false, true> : k_rt<TX, TA, R, BS, UPX, true>;
         allow_lds(kern);
         kern<<<(unsigned)nblk, BS, shm, s>>>(a);
     }
@@ -2089,6 +2126,15 @@ static void launch_variant(ed_ham_s *h, const ApplyArgs<TX, TA> &a, int v, hipSt
         case 33: launch_gtile<TX, TA, 1, 512>(h, a, 8192, s); break;
         case 34: launch_gtile<TX, TA, 1, 512>(h, a, 8192, s, 20); break;
         case 35: launch_gtile<TX, TA, 1, 512>(h, a, 8192, s, 128); break;
+        case 36: launch_rt<TX, TA, 1, 1024>(h, a, s, V.wcap); break;
+        case 37:
+            launch_rt<TX, TA, 2, 1024, false>(h, a, s, 0);
+            launch_upt<TX, TA>(h, a, V.band, V.rw, s);
+            break;
+        case 38:
+            launch_rt<TX, TA, 1, 1024, false>(h, a, s, 0);
+            launch_upt<TX, TA>(h, a, V.band, V.rw, s);
+            break;
         default: fail(ED_EINVAL, "bad apply variant %d", v);
     }
 }
@@ -2100,6 +2146,9 @@ static bool variant_fits(const ed_ham_s *h, int v, size_t elem) {
     if (V.kind == 4 && (!h->sp[1].pk_ok || h->sp[0].max_hops > 32 || h->xl_max > 16 || h->sp[1].nmv > 8))
         return false;
     if (V.kind == 6 && (!h->sp[1].pk_ok || h->sp[0].max_hops > 32 || h->xl_max > 16 || h->koff > 4)) return false;
+    if (V.kind == 14 && (h->grouped || !h->sp[1].pk_ok || h->xl_max > 16 || h->koff > 4 || h->sp[0].nnz == 0 ||
+                         h->sp[0].max_hops > kUptHops || h->D >= ((int64_t)1 << 32)))
+        return false;
     if (V.kind == 8 && (h->sp[0].nnz == 0 || cs_kmax(h) == 0 || cs_nmv(h) < 0 || (h->nx > 0 && cs_xmax(h) == 0)))
         return false;
     if (V.kind == 8 && V.BS > 512 && cs_kmax(h) > 16) return false;
@@ -2165,6 +2214,11 @@ static void tune(ed_ham_s *h, const void *x, void *y, hipStream_t s) {
     int bestv = -1;
     for (int v = 0; v < kNumVariants; ++v) {
         if (!variant_fits(h, v, elem)) continue;
+        // row pass + band pass reads and writes y once more to spare partner rows
+        // from HBM: worth timing only where x is larger than the Infinity Cache
+        // (4x4 Hubbard, 663 MB: 1.88 ms against 2.26 for the best single pass;
+        // 257 MB: 0.63 against 0.48)
+        if (kVariants[v].kind == 14 && (size_t)h->D * elem < ((size_t)300 << 20)) continue;
         launch_store(h, v, x, y, s);  // warm-up
         ED_HIP(hipEventRecord(e0, s));
         for (int k = 0; k < 3; ++k) launch_store(h, v, x, y, s);
