@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <cstring>
 #include <string>
@@ -247,7 +248,12 @@ struct ed_ham_s {
     std::vector<std::pair<int64_t, ed::DevMem *>> items;
     std::vector<int64_t> item_counts;
     std::vector<ed::TilePlan *> tplans;
+    // pinned host memory of the one solve at a time that holds it (HostBox); a
+    // solve that finds it taken copies through pageable memory
+    std::atomic<bool> box_busy{false};
+    double *box = nullptr;
     ~ed_ham_s() {
+        if (box) (void)hipHostFree(box);
         for (auto &w : windows) delete w.second;
         for (auto &w : items) delete w.second;
         for (auto *t : tplans) delete t;

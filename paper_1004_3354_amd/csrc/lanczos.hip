@@ -887,11 +887,28 @@ __device__ void k_tridiag_lowest_body(const double *alpha, const double *beta, i
     __syncthreads();
 }
 
+// host: where the first three numbers go as well, for a host that waits for them
+// (pinned memory), or null
 __global__ __launch_bounds__(256) void k_tridiag_lowest(const double *alpha, const double *beta, int m, double *out,
-                                                        NormJob nj) {
+                                                        double *host, NormJob nj) {
     __shared__ double sh[256];
     if (nj.n > 0) norm_job(nj, sh);  // beta[m - 1], read by the thread that writes it
     k_tridiag_lowest_body(alpha, beta, m, out);
+    if (host && threadIdx.x == 0)  // written by this thread
+        for (int i = 0; i < 3; ++i) host[i] = out[i];
+}
+
+// Up to three short arrays copied by one launch, between device and pinned host
+// memory: a restart's tables go over in one kernel of about 3 us instead of a
+// copy of 10 us each.
+struct Words {
+    const double *src[3];
+    double *dst[3];
+    int n[3];
+};
+__global__ __launch_bounds__(256) void k_words(Words w) {
+    for (int q = 0; q < 3; ++q)
+        for (int i = threadIdx.x; i < w.n[q]; i += 256) w.dst[q][i] = w.src[q][i];
 }
 
 // coef[i] = s_i * sigma_i for the Ritz combination psi = sum_i s_i v_i
@@ -1179,6 +1196,51 @@ static size_t layout(Work &w, char *base, int64_t D, size_t elem, int m, int kma
 }
 
 // ----------------------------------------------------------------- solver --
+// The handle's pinned host memory, held by one solve at a time: the kernels write
+// what the host waits for straight into it, and an event marks the moment, so
+// that further work can be queued before the host waits.  Against copies through
+// pageable memory (each 10-20 us of host time): D = 4900 FP64 2.93 -> 2.43 ms,
+// four levels at D = 853 776 57.3 -> 51.8 ms.  p stays null when
+// another solve on the handle holds it or the allocation fails; the solve then
+// copies through pageable memory.
+struct HostBox {
+    static constexpr int kTri = 0;                    // theta, residual, beta
+    static constexpr int kIn = 8;                     // alpha, beta, sigma^2 for a restart plan; then its norm
+    static constexpr int kOut = kIn + 3 * kIRMaxIn;   // the new alpha, beta, sigma^2
+    static constexpr int kCoef = kOut + 3 * (kIRMaxIn + 1);
+    static constexpr int kWords = kCoef + kIRMaxIn * kIRMaxOut;
+    ed_ham_s *h = nullptr;
+    double *p = nullptr;
+    hipEvent_t ev = nullptr;
+    hipStream_t st = nullptr;
+    bool idle = false;  // nothing queued touches p any more
+    HostBox() = default;
+    HostBox(const HostBox &) = delete;
+    HostBox &operator=(const HostBox &) = delete;
+    void take(ed_ham_s *ham, hipStream_t s) {
+        st = s;
+        if (ham->box_busy.exchange(true, std::memory_order_acquire)) return;
+        h = ham;
+        if (!ham->box && hipHostMalloc((void **)&ham->box, kWords * sizeof(double), hipHostMallocCoherent) != hipSuccess) {
+            (void)hipGetLastError();
+            ham->box = nullptr;
+        }
+        if (ham->box && hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
+            (void)hipGetLastError();
+            ev = nullptr;
+        }
+        if (ev) p = ham->box;
+    }
+    // the work queued so far is done
+    void mark() { ED_HIP(hipEventRecord(ev, st)); }
+    void wait() { ED_HIP(hipEventSynchronize(ev)); }
+    ~HostBox() {
+        if (p && !idle) (void)hipStreamSynchronize(st);  // left by an error
+        if (ev) (void)hipEventDestroy(ev);
+        if (h) h->box_busy.store(false, std::memory_order_release);
+    }
+};
+
 struct Solver {
     ed_ham_s *h;               // the operator the iteration runs on
     ed_ham_s *flat = nullptr;  // the rank-order handle when h is its grouped twin
@@ -1188,6 +1250,7 @@ struct Solver {
     int nlock = 0;
     std::vector<double> lock_sig2;
     double moved = 0.0;  // algorithmic bytes of the vector kernels launched so far
+    HostBox box;
     void count(double nvec) { moved += nvec * (double)h->D * (double)w.elem; }
 
     NormJob pending;     // norm of the newest vector, not finished yet
@@ -1313,9 +1376,36 @@ struct Solver {
     }
     // lowest eigenpair of T_m, after the norm of the last step if that is pending
     void tridiag_lowest(int m) {
-        k_tridiag_lowest<<<1, 256, 0, s>>>(w.alpha, w.beta, m, w.tri, take_norm());
+        k_tridiag_lowest<<<1, 256, 0, s>>>(w.alpha, w.beta, m, w.tri, box.p ? box.p + HostBox::kTri : nullptr,
+                                           take_norm());
         ED_LAUNCH_CHECK();
+        if (box.p) box.mark();
     }
+    // its result on the host; work queued since tridiag_lowest is not waited for
+    // (with pinned memory)
+    void tridiag_result(double *tv) {
+        if (box.p) {
+            box.wait();
+            std::memcpy(tv, box.p + HostBox::kTri, 3 * sizeof(double));
+        } else {
+            ED_HIP(hipMemcpyAsync(tv, w.tri, 3 * sizeof(double), hipMemcpyDeviceToHost, s));
+            ED_HIP(hipStreamSynchronize(s));
+        }
+    }
+    // One step of a cycle: S_{j+1} from S_j.
+    void step(const std::vector<void *> &kr, int j) {
+        apply_launch(h, kr[j], kr[j + 1], s);
+        count(2);
+        orthogonalise(j, kr[j + 1], kr[j]);
+    }
+    // Queue the step after a check before waiting for the check's result?  Until
+    // the host has the answer and the next launches arrive the GPU would be idle
+    // for about 10 us; a step queued in vain, once per eigenpair, costs more than
+    // all those gaps when vectors are large.  Whole solves, waiting against a step
+    // queued: D = 4900 FP64 2.43 and 2.29 ms, D = 853 776 FP64 24.8 and 24.6 ms
+    // (basis 120), 11.1 and 10.8 ms (basis 20), 51.8 and 51.1 ms (four levels).
+    // Above 8 MB per vector the gap is under 1% of the steps between two checks.
+    bool ahead() const { return box.p && (double)h->D * (double)w.elem <= 8e6; }
     void combine(int vbeg, const double *coef, int nvec, void *out) {  // out = sum coef_i S_i
         count(nvec + 1);
         lincomb_any(vbeg, coef, DirectCoef{}, nvec, out, 1, -1.0, nullptr, nullptr);
@@ -1374,6 +1464,37 @@ struct Solver {
         return n2;
     }
 
+    // Up to three short arrays between host and device, through the pinned words
+    // from `at` on: to the host (done on return), or to the device (in stream
+    // order; the same words are used again only after a later result has been
+    // waited for).
+    void move_words(Words wd, int at, bool to_host) {
+        if (!box.p) {
+            for (int q = 0; q < 3; ++q)
+                if (wd.n[q] > 0)
+                    ED_HIP(hipMemcpyAsync(wd.dst[q], wd.src[q], (size_t)wd.n[q] * sizeof(double),
+                                          to_host ? hipMemcpyDeviceToHost : hipMemcpyHostToDevice, s));
+            ED_HIP(hipStreamSynchronize(s));
+            return;
+        }
+        Words dev = wd;
+        double *p = box.p + at;
+        for (int q = 0; q < 3; p += wd.n[q], ++q) {
+            if (to_host) dev.dst[q] = p;
+            else {
+                dev.src[q] = p;
+                if (wd.n[q] > 0) std::memcpy(p, wd.src[q], (size_t)wd.n[q] * sizeof(double));
+            }
+        }
+        k_words<<<1, 256, 0, s>>>(dev);
+        ED_LAUNCH_CHECK();
+        if (!to_host) return;
+        box.mark();
+        box.wait();
+        for (int q = 0; q < 3; ++q)
+            if (wd.n[q] > 0) std::memcpy(wd.dst[q], dev.dst[q], (size_t)wd.n[q] * sizeof(double));
+    }
+
     // One eigenpair by restarted Lanczos.  `out` receives the Ritz vector
     // normalised to 1 (it must not be one of the slots).  Returns the status.
     // fresh >= 0: start from the SplitMix64 normal stream `fresh` instead of v0.
@@ -1385,15 +1506,13 @@ struct Solver {
     bool implicit_restart(int m, int k, bool *breakdown) {
         *breakdown = false;
         std::vector<double> al((size_t)m), be((size_t)m), sg((size_t)m + 1);
-        ED_HIP(hipMemcpyAsync(al.data(), w.alpha, (size_t)m * sizeof(double), hipMemcpyDeviceToHost, s));
-        ED_HIP(hipMemcpyAsync(be.data(), w.beta, (size_t)m * sizeof(double), hipMemcpyDeviceToHost, s));
         // Krylov entries of the pointer and sigma tables follow the nlock locked ones
-        ED_HIP(hipMemcpyAsync(sg.data(), w.sig2 + nlock, (size_t)(m + 1) * sizeof(double), hipMemcpyDeviceToHost, s));
-        ED_HIP(hipStreamSynchronize(s));
+        move_words({{w.alpha, w.beta, w.sig2 + nlock}, {al.data(), be.data(), sg.data()}, {m, m, m + 1}}, HostBox::kIn,
+                   true);
         std::vector<double> C, a2, b2, ev;
         if (!ir_plan(al, be, sg, m, k, C, a2, b2, ev)) return false;
         const int nin = m + 1, nout = k + 1;
-        ED_HIP(hipMemcpyAsync(w.rcoef, C.data(), C.size() * sizeof(double), hipMemcpyHostToDevice, s));
+        move_words({{C.data()}, {w.rcoef}, {(int)C.size()}}, HostBox::kCoef, false);
         count(nin + nout);
         if (h->prec == ED_FP64)
             launch_restart_combine<double>((const double *const *)w.vp + nlock, w.rcoef, nin, nout, h->D, w.partials,
@@ -1405,8 +1524,7 @@ struct Solver {
         k_finalize_dots_par<<<1, 256, 0, s>>>(w.partials, w.nblk, nullptr, w.raw, nullptr, nullptr, 0, nullptr, 0);
         ED_LAUNCH_CHECK();
         double n2 = 0.0;
-        ED_HIP(hipMemcpyAsync(&n2, w.raw, sizeof(double), hipMemcpyDeviceToHost, s));
-        ED_HIP(hipStreamSynchronize(s));
+        move_words({{w.raw}, {&n2}, {1}}, HostBox::kIn, true);
         std::vector<double> na((size_t)m + 2, 0.0), nbv((size_t)m + 2, 0.0), ns((size_t)m + 1, 0.0);
         for (int i = 0; i < k; ++i) {
             na[i] = a2[i];
@@ -1418,15 +1536,14 @@ struct Solver {
             *breakdown = true;
         nbv[k - 1] = *breakdown ? 0.0 : std::sqrt(n2);
         ns[k] = *breakdown ? 0.0 : 1.0 / n2;
-        ED_HIP(hipMemcpyAsync(w.alpha, na.data(), na.size() * sizeof(double), hipMemcpyHostToDevice, s));
-        ED_HIP(hipMemcpyAsync(w.beta, nbv.data(), nbv.size() * sizeof(double), hipMemcpyHostToDevice, s));
-        ED_HIP(hipMemcpyAsync(w.sig2 + nlock, ns.data(), ns.size() * sizeof(double), hipMemcpyHostToDevice, s));
+        move_words({{na.data(), nbv.data(), ns.data()}, {w.alpha, w.beta, w.sig2 + nlock}, {m + 2, m + 2, m + 1}},
+                   HostBox::kOut, false);
         if (o.reorth == 3 && nlock == 0) {
             std::vector<double> G((size_t)(m + 1) * (m + 1), 0.0);
             for (int i = 0; i < k; ++i) G[(size_t)i * (m + 1) + i] = 1.0;
             ED_HIP(hipMemcpyAsync(w.gram, G.data(), G.size() * sizeof(double), hipMemcpyHostToDevice, s));
+            ED_HIP(hipStreamSynchronize(s));
         }
-        ED_HIP(hipStreamSynchronize(s));
         return true;
     }
 
@@ -1526,30 +1643,38 @@ struct Solver {
                 ED_LAUNCH_CHECK();
             }
             int j = jstart;
-            bool cycle_done = false;
+            bool cycle_done = false, queued = false;
             for (; j < m; ++j) {
-                void *Y = kr[j + 1];
-                apply_launch(h, kr[j], Y, s);
-                count(2);
-                orthogonalise(j, Y, kr[j]);
+                if (!queued) step(kr, j);
+                queued = false;
                 ++total;
                 const bool full = (j + 1 == m);
                 const bool check = j == 0 || ((j + 1) % o.check_every == 0) || full || total >= o.max_iter;
                 if (!check) continue;
                 tridiag_lowest(j + 1);
+                const double moved_here = moved;
+                if (ahead() && !full && total < o.max_iter) {
+                    step(kr, j + 1);
+                    queued = true;
+                }
                 double tv[3];
-                ED_HIP(hipMemcpyAsync(tv, w.tri, sizeof(tv), hipMemcpyDeviceToHost, s));
-                ED_HIP(hipStreamSynchronize(s));
+                tridiag_result(tv);
                 theta = tv[0];
                 resid = tv[1];
                 jlast = j + 1;
                 const double scale = std::max(std::fabs(theta), 1.0);
                 const bool brk = std::fabs(tv[2]) <= 64.0 * eps * scale;
-                if (!std::isfinite(theta) || !std::isfinite(resid))
+                if (!std::isfinite(theta) || !std::isfinite(resid)) {
+                    if (queued) ED_HIP(hipStreamSynchronize(s));
                     fail(ED_EDEVICE, "non-finite Lanczos coefficients (alpha/beta) at step %d", total);
+                }
                 if (resid <= o.tol * scale || brk || (full && spans)) {
                     converged = true;
                     cycle_done = true;
+                    if (queued) {  // a step too many: S_{j+2}, alpha_{j+1} and beta_{j+1} are not read
+                        moved = moved_here;
+                        (void)take_norm();
+                    }
                     break;
                 }
                 if (total >= o.max_iter || full) {
@@ -1578,8 +1703,7 @@ struct Solver {
                     k_ritz_coef<<<1, 256, 0, s>>>(w.tri + 3, w.sig2 + nlock, jlast, w.coef);
                     ED_LAUNCH_CHECK();
                     double tv[3];
-                    ED_HIP(hipMemcpyAsync(tv, w.tri, sizeof(tv), hipMemcpyDeviceToHost, s));
-                    ED_HIP(hipStreamSynchronize(s));
+                    tridiag_result(tv);
                     theta = tv[0];
                     resid = 0.0;
                     combine(nlock, w.coef, jlast, out);
@@ -1748,6 +1872,7 @@ static ed_status solve(ed_ham_t h, int k, const ed_lanczos_opts *opts, const voi
         // the boundary
         sv.h = (sv.o.layout == 0 && h->twin) ? h->twin : h;
         if (sv.h != h) sv.flat = h;
+        sv.box.take(sv.h, sv.s);
         const size_t need = ws_needed(h, sv.o, k, locked_in_ws);
         if (ws_bytes < need) fail(ED_EINVAL, "workspace of %zu bytes is smaller than the %zu needed", ws_bytes, need);
         layout(sv.w, (char *)ws, h->D, h->prec == ED_FP64 ? 8 : 4, sv.o.max_basis, k, locked_in_ws);
@@ -1793,6 +1918,7 @@ static ed_status solve(ed_ham_t h, int k, const ed_lanczos_opts *opts, const voi
         else
             for (int e = 0; e < k; ++e) sv.convert_in_place(sv.w.locked[e], 1);
         ED_HIP(hipStreamSynchronize(sv.s));
+        sv.box.idle = true;
     });
     if (st != ED_OK) return st;
     return result;

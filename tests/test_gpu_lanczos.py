@@ -300,6 +300,48 @@ def test_two_pass_reorthogonalisation_sizes(ns, nn, basis, keep, prec):
         assert _rel(a, r) <= TOL[prec], (E, e_ref)
 
 
+@pytest.mark.parametrize("basis,keep,check,reorth", [
+    (20, 6, 1, 2),      # a step queued after every check, restarts in between
+    (21, 0, 4, 3),      # restarts from the Ritz vector, the basis full between two checks
+    (40, 8, 1000, 3),   # checks only when the basis is full: nothing queued ahead but after the first
+], ids=["each", "ritz", "full"])
+def test_solves_sharing_a_handle(basis, keep, check, reorth):
+    """Two solves at once on one handle, of which one at a time holds the pinned
+    words (the other copies through pageable memory), against the same solve
+    alone: every number is the same, and the levels are the oracle's."""
+    import threading
+
+    ed = gpu_ed()
+    phys = wl.aim(7, 2.0, -1.0, seed=23)
+    b, H = build(phys, 4, 3, 0)
+    v0 = _v0(b.D, 0, 4)
+    o = ed.options(tol=1e-10, reorth=reorth, max_basis=basis, keep=keep, check_every=check, max_iter=3000, refine=0)
+    E1, i1 = H.lowest(2, v0, o)
+    for a, r in zip(E1, orc.lowest_k(sector(phys, 4, 3), 2, tol=1e-13)):
+        assert _rel(a, r) <= TOL[0], E1
+    start, got = threading.Barrier(2), [[], []]
+    torch.cuda.synchronize()
+
+    def work(t):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            start.wait(timeout=60)
+            for _ in range(4):
+                got[t].append(H.lowest(2, v0, o))
+
+    pool = [threading.Thread(target=work, args=(t,)) for t in range(2)]
+    for t in pool:
+        t.start()
+    for t in pool:
+        t.join()
+    for runs in got:
+        assert len(runs) == 4
+        for E, i in runs:
+            assert list(E) == list(E1)
+            for x, y in zip(i, i1):
+                assert (x["iters"], x["restarts"], x["residual"], x["traffic"]) == (
+                    y["iters"], y["restarts"], y["residual"], y["traffic"])
+
+
 @pytest.mark.parametrize("m,reorth", [(1, 3), (2, 3), (3, 3), (5, 3), (6, 3), (44, 3), (100, 3), (301, 0)])
 def test_tridiagonal_lowest_eigenpair(m, reorth):
     """The device eigensolve of T_m against numpy: theta to the rounding of T,
