@@ -434,10 +434,10 @@ void ed_levels_free(ed_levels_t L);
  * sequence of batched kernels captured once in a hipGraph -- while each
  * sector keeps its own step index, so sectors converge (masked off on the
  * device), fill their basis and restart independently.  A sector whose basis
- * is full waits until the host restarts it (at most check_every steps later):
- * implicitly with opts->keep vectors when keep > 0 (exact shifts, as
- * ed_lanczos_ground), else from its Ritz vector; all waiting sectors restart in
- * one batched combination.  opts->reorth 0..3 as for ed_lanczos_ground.  The
+ * is full restarts on the device at the end of that step: implicitly with
+ * opts->keep vectors when keep > 0 (exact shifts, as ed_lanczos_ground), else
+ * from its Ritz vector.  opts->reorth 0..3 as for ed_lanczos_ground, except that
+ * 2 is two passes over the whole basis.  The
  * apply runs over row tiles of about T output elements per workgroup, T picked
  * on the first step by timing candidates (ED_BATCH_TILE=<T> forces one); the
  * vector kernels run over chunks of at most 8192 elements of one sector.
@@ -457,7 +457,7 @@ ed_status ed_lanczos_ground_batched(int nsec, const ed_ham_t *hs, const ed_lancz
                                     double *E0, ed_info *info, void *stream);
 int64_t ed_batched_last_tile(void);
 /* Figures of the last batched run in this process (not thread-safe): steps =
- * replayed graph steps, restart_events = batched restart launches, bytes =
+ * replayed graph steps, restart_events = steps in which some sector restarted, bytes =
  * algorithmic bytes moved (per step and sector: x read, y written, and per
  * projection pass the nv projected vectors read twice plus Y read twice and
  * written once; per restart the inputs read and outputs written).  Any output

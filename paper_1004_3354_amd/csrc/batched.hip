@@ -7,9 +7,9 @@
 // hipGraph and replayed.  Each sector keeps its own step index, state and
 // basis in device memory, so sectors converge, fill their basis and restart
 // independently: a converged sector drops out through its device flag, a
-// sector whose basis is full waits (masked) until the host restarts it --
-// implicitly (exact shifts, keeping `keep` vectors) or from its Ritz vector --
-// with one batched combination kernel over all waiting sectors.
+// sector whose basis is full restarts at the end of the same step -- implicitly
+// (exact shifts, keeping `keep` vectors) or from its Ritz vector -- planned by one
+// workgroup per sector and rebuilt by a batched combination kernel.
 //
 // Work decomposition (the paper's observation that equal splits of the matrix
 // give unequal work, end of Section 3.2, is the reason the tiles are sized per
@@ -635,7 +635,8 @@ __global__ __launch_bounds__(kBBS) void kb_update_v4(const BSec<TX, TX> *secs, c
 
 // End of a step, per running sector: beta_j and sigma_{j+1}^2 from the norm sum,
 // lowest eigenpair of T_{j+1}, convergence test; then the sector either stops
-// (converged or broken down), waits for a restart (basis full) or moves on.
+// (converged or broken down), is marked for the restart that ends the step (basis
+// full) or moves on.
 __global__ __launch_bounds__(256) void kb_tridiag(BState st, BDims dm, double tol) {
     const int s = blockIdx.x;
     if (st.active[s] != 1) return;

@@ -432,7 +432,7 @@ def lanczos_ground_batched(hams: Sequence[Hamiltonian], opts=None, seed: int = 0
 
 def batched_last_stats():
     """Figures of the last batched run in this process: graph-replayed steps,
-    restart events, apply tile size and algorithmic bytes moved (x read and y
+    steps in which a sector restarted, apply tile size and algorithmic bytes moved (x read and y
     written per step, the projection window read twice and Y read twice and
     written once per pass, and every restart's inputs and outputs)."""
     steps, ev, nb = ctypes.c_int64(), ctypes.c_int64(), ctypes.c_double()
