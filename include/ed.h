@@ -436,8 +436,7 @@ void ed_levels_free(ed_levels_t L);
  * device), fill their basis and restart independently.  A sector whose basis
  * is full restarts on the device at the end of that step: implicitly with
  * opts->keep vectors when keep > 0 (exact shifts, as ed_lanczos_ground), else
- * from its Ritz vector.  opts->reorth 0..3 as for ed_lanczos_ground, except that
- * 2 is two passes over the whole basis.  The
+ * from its Ritz vector.  opts->reorth 0..3 as for ed_lanczos_ground.  The
  * apply runs over row tiles of about T output elements per workgroup, T picked
  * on the first step by timing candidates (ED_BATCH_TILE=<T> forces one); the
  * vector kernels run over chunks of at most 8192 elements of one sector.
