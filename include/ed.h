@@ -448,7 +448,9 @@ void ed_levels_free(ed_levels_t L);
  * workspace of at least ed_batched_workspace_bytes.  max_basis = 0 gives 60
  * vectors per sector (at most 1000; keep is used with at most 256).  max_iter
  * bounds the replayed steps.  Synchronous.  ED_ENOCONV if some sector was
- * still unconverged at max_iter (all E0 still written). */
+ * still unconverged at max_iter (all E0 still written).  EINVAL: a start vector
+ * that is zero or not finite.  EDEVICE: a sector's coefficients became non-finite;
+ * its E0 is NaN, its info not converged, and the other sectors' are written. */
 ed_status ed_batched_workspace_bytes(int nsec, const ed_ham_t *hs, const ed_lanczos_opts *opts,
                                      size_t *bytes);
 ed_status ed_lanczos_ground_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts *opts,

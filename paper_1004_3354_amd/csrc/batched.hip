@@ -75,7 +75,8 @@ struct RChunk {
 struct BState {
     double *sig2, *gamma, *alpha, *beta, *tri, *raw, *gram, *coef, *a2b2;
     double *theta, *resid;
-    int *active;  // 0 done, 1 running, 2 basis full (restarts at the end of the step)
+    int *active;  // 0 done, 1 running, 2 basis full (restarts at the end of the step), -1 failed
+                  // (zero or non-finite vector, non-finite coefficients)
     int *jcur;    // step index of the running cycle
     int *nsteps;  // size of the tridiagonal matrix behind theta / tri
     int *iters;   // steps taken, all cycles
@@ -636,8 +637,9 @@ __global__ __launch_bounds__(kBBS) void kb_update_v4(const BSec<TX, TX> *secs, c
 
 // End of a step, per running sector: beta_j and sigma_{j+1}^2 from the norm sum,
 // lowest eigenpair of T_{j+1}, convergence test; then the sector either stops
-// (converged or broken down), is marked for the restart that ends the step (basis
-// full) or moves on.
+// (converged, broken down, or failed on a non-finite coefficient: one in T makes the
+// residual estimate NaN, whatever theta is), is marked for the restart that ends the
+// step (basis full) or moves on.
 __global__ __launch_bounds__(256) void kb_tridiag(BState st, BDims dm, double tol) {
     const int s = blockIdx.x;
     if (st.active[s] != 1) return;
@@ -674,7 +676,8 @@ __global__ __launch_bounds__(256) void kb_tridiag(BState st, BDims dm, double to
         st.iters[s] += 1;
         st.nvsum[s] += (double)(j + 1 - win_begin(dm.reorth, j));
         const bool brk = fabs(bl) <= 64.0 * 2.220446049250313e-16 * scale;
-        if (res <= tol * scale || brk || !isfinite(theta)) st.active[s] = 0;
+        if (!isfinite(theta) || !isfinite(res)) st.active[s] = -1;
+        else if (res <= tol * scale || brk) st.active[s] = 0;
         else if (m == dm.m) st.active[s] = 2;
         else st.jcur[s] = j + 1;
     }
@@ -903,7 +906,8 @@ __global__ __launch_bounds__(256) void kb_plan(BState st, BDims dm, int keep, do
 // tridiagonal block from a2b2, beta_{k-1} = ||f||, the Gram block of the kept
 // vectors = I, step k; when ||f|| vanishes the kept vectors span an invariant
 // subspace and the sector finishes on T_k.  The Ritz vector's coefficients are
-// those on the new basis from here on.  Every request is cleared.
+// those on the new basis from here on.  A new S_0 or residual whose norm is not
+// finite, or an S_0 of norm zero, fails the sector.  Every request is cleared.
 template <typename TX>
 __global__ __launch_bounds__(256) void kb_restart_fin(const BSec<TX, TX> *secs, BState st, BDims dm,
                                                       const double *part) {
@@ -914,7 +918,7 @@ __global__ __launch_bounds__(256) void kb_restart_fin(const BSec<TX, TX> *secs, 
         if (threadIdx.x == 0) st.rnout[s] = 0;
         return;
     }
-    __shared__ int brk_s;
+    __shared__ int brk_s, bad_s;
     __shared__ double sh[4];
     const int k = st.rnout[s] - 1;  // implicit: kept vectors
     double n2 = 0.0;
@@ -945,7 +949,8 @@ __global__ __launch_bounds__(256) void kb_restart_fin(const BSec<TX, TX> *secs, 
     if (threadIdx.x == 0) {
         const double scale = fmax(fabs(st.theta[s]), 1.0);
         const double lim = 64.0 * 2.220446049250313e-16 * scale;
-        brk_s = (mode == 2 && !(n2 > lim * lim)) || (mode == 1 && !(n2 > 0.0));
+        brk_s = mode == 2 && !(n2 > lim * lim);
+        bad_s = !isfinite(n2) || (mode == 1 && !(n2 > 0.0));
     }
     __syncthreads();
     if (mode == 1) {
@@ -954,7 +959,14 @@ __global__ __launch_bounds__(256) void kb_restart_fin(const BSec<TX, TX> *secs, 
             st.tri[(int64_t)s * dm.mt + 3] = 1.0;
             st.nsteps[s] = 1;
             st.jcur[s] = 0;
-            st.active[s] = brk_s ? 0 : 1;
+            st.active[s] = bad_s ? -1 : 1;
+            st.rnout[s] = 0;
+        }
+        return;
+    }
+    if (bad_s) {
+        if (threadIdx.x == 0) {
+            st.active[s] = -1;
             st.rnout[s] = 0;
         }
         return;
@@ -1328,7 +1340,14 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     std::fill(h_rmode.begin(), h_rmode.end(), 1);
     for (int q = 0; q < nsec; ++q) h_coef[(size_t)q * dm.mc] = 1.0;
     launch_request();
-    ED_HIP(hipStreamSynchronize(s));
+    std::vector<int> act(S), restarts(S, 0);
+    auto fetch_active = [&]() {
+        ED_HIP(hipMemcpyAsync(act.data(), st.active, S * 4, hipMemcpyDeviceToHost, s));
+        ED_HIP(hipStreamSynchronize(s));
+    };
+    fetch_active();
+    for (int q = 0; q < nsec; ++q)
+        if (act[q] < 0) fail(ED_EINVAL, "start vector of batched sector %d is zero or not finite", q);
 
     // ---- tile schedule: time a few tile sizes on slot 0 -> slot 1 (every sector at step 0)
     std::vector<int64_t> cands = {4096, 8192};
@@ -1427,23 +1446,21 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     ED_HIP(hipStreamEndCapture(cs, &graph));
     ED_HIP(hipGraphInstantiate(&gexec, graph, nullptr, nullptr, 0));
 
-    std::vector<int> act(S), restarts(S, 0);
     int64_t launches = 0;
     const int every = std::max(1, o.check_every);
     while (launches < o.max_iter) {
         const int n = (int)std::min<int64_t>(every, o.max_iter - launches);
         for (int r = 0; r < n; ++r) ED_HIP(hipGraphLaunch(gexec, s));
         launches += n;
-        ED_HIP(hipMemcpyAsync(act.data(), st.active, S * 4, hipMemcpyDeviceToHost, s));
-        ED_HIP(hipStreamSynchronize(s));
-        if (std::all_of(act.begin(), act.end(), [](int q) { return q == 0; })) break;
+        fetch_active();
+        if (std::all_of(act.begin(), act.end(), [](int q) { return q <= 0; })) break;
     }
     (void)hipGraphExecDestroy(gexec);
     (void)hipGraphDestroy(graph);
     (void)hipStreamDestroy(cs);
 
     // ---- final Ritz vectors (into S_0) for every sector, FP64 Rayleigh quotients
-    ED_HIP(hipMemcpyAsync(act.data(), st.active, S * 4, hipMemcpyDeviceToHost, s));
+    fetch_active();
     fetch_state();
     std::fill(h_rnout.begin(), h_rnout.end(), 0);
     for (int q = 0; q < nsec; ++q) ritz_request(q, 3);
@@ -1494,7 +1511,8 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
         bytes += bq + rvec[q] * (double)B.D[q] * (double)B.elem;
         const bool conv = act[q] == 0;
         allconv &= conv;
-        const double rqi = (o.refine && rqv[2 * q + 1] > 0.0) ? rqv[2 * q] / rqv[2 * q + 1] : theta[q];
+        if (act[q] < 0) theta[q] = resid[q] = std::nan("");
+        const double rqi = act[q] >= 0 && o.refine && rqv[2 * q + 1] > 0.0 ? rqv[2 * q] / rqv[2 * q + 1] : theta[q];
         E0[q] = rqi;
         if (info) {
             ed_info f{};
@@ -1515,6 +1533,9 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     g_last.steps = launches;
     g_last.restart_events = evs[0];
     g_last.bytes = bytes;
+    for (int q = 0; q < nsec; ++q)
+        if (act[q] < 0)
+            fail(ED_EDEVICE, "non-finite Lanczos coefficients (alpha/beta) in batched sector %d, step %d", q, iters[q]);
     return allconv ? ED_OK : ED_ENOCONV;
 }
 

@@ -205,3 +205,66 @@ def test_batched_restart_plans(basis, keep, reorth):
         assert abs(e - ref) <= 1e-10 * max(1.0, abs(ref)), (s, e, ref)
     if basis <= 17:
         assert info[0]["restarts"] > 0
+
+
+@pytest.mark.parametrize("keep", [0, 4], ids=["ritz", "implicit"])
+@pytest.mark.parametrize("fault", [0.0, float("nan"), float("inf")], ids=["zero", "nan", "inf"])
+def test_batched_start_vector_must_be_finite(fault, keep):
+    """A zero or non-finite start vector of one sector is refused, as the
+    single-sector solver refuses it, and names the sector; the same call with
+    a valid vector in its place still solves."""
+    ed = gpu_ed()
+    phys = wl.aim(5, 2.0, -1.0, seed=3)
+    secs = [(3, 3), (2, 3), (3, 2)]
+    hs = _hams(phys, secs, 0)
+    o = ed.options(tol=1e-10, max_basis=12, keep=keep, max_iter=2000)
+    v0s = []
+    for i, h in enumerate(hs):
+        v = torch.empty(h.D, dtype=torch.float64, device="cuda")
+        ed.fill_random(v, 5 + i, 1)
+        v0s.append(v)
+    E, _ = ed.lanczos_ground_batched(hs, o, v0s=v0s)
+    good = v0s[1].clone()
+    if fault == 0.0:
+        v0s[1].zero_()
+    else:
+        v0s[1][7] = fault
+    with pytest.raises(ed.EDError) as err:
+        ed.lanczos_ground_batched(hs, o, v0s=v0s)
+    assert err.value.status == ed.ED_EINVAL and "sector 1" in str(err.value)
+    with pytest.raises(ed.EDError) as err:
+        hs[1].lanczos_ground(v0s[1], o)
+    assert err.value.status == ed.ED_EINVAL
+    E2, info = ed.lanczos_ground_batched(hs, o, v0s=[v0s[0], good, v0s[2]])
+    assert all(i["converged"] == 1 for i in info)
+    assert np.all(np.abs(E2 - E) <= 1e-10 * np.maximum(1.0, np.abs(E)))
+
+
+@pytest.mark.parametrize("basis,keep", [(4, 0), (6, 3), (40, 0)], ids=["ritz", "implicit", "one-basis"])
+def test_batched_sector_with_overflowing_coefficients(basis, keep):
+    """A sector whose product overflows FP32 fails instead of reporting a converged
+    energy: EDEVICE, its E0 NaN and not converged, the other sectors' energies those
+    of a batch without it."""
+    import ctypes
+    ed = gpu_ed()
+    phys = wl.aim(5, 2.0, -1.0, seed=3)
+    good = models.params_from_model(phys)
+    bad = dict(good)
+    bad["eps"] = np.full((2, 6), 1e39)   # finite in FP64, infinite in FP32
+    secs = [(3, 3), (2, 3), (3, 2)]
+    hs = [ed.Hamiltonian(bad if i == 1 else good, ed.Basis(6, *s), 1) for i, s in enumerate(secs)]
+    o = ed.options(tol=1e-7, max_basis=basis, keep=keep, max_iter=2000)
+    ref, _ = ed.lanczos_ground_batched([hs[0], hs[2]], o)
+    n = ctypes.c_size_t()
+    handles = (ctypes.c_void_p * 3)(*[h._h for h in hs])
+    hp = ctypes.cast(handles, ctypes.c_void_p)
+    assert ed._lib.ed_batched_workspace_bytes(3, hp, ctypes.byref(o), ctypes.byref(n)) == ed.ED_OK
+    ws = torch.empty(n.value, dtype=torch.uint8, device="cuda")
+    E, infos = np.zeros(3), (ed.ed_info * 3)()
+    st = ed._lib.ed_lanczos_ground_batched(3, hp, ctypes.byref(o), None, 0, ws.data_ptr(), ws.numel(),
+                                           E.ctypes.data_as(ctypes.c_void_p), ctypes.cast(infos, ctypes.c_void_p), None)
+    assert st == ed.ED_EDEVICE and b"sector 1" in ed._lib.ed_last_error()
+    assert np.isnan(E[1])
+    assert [i.converged for i in infos] == [1, 0, 1]
+    for e, r in zip(E[[0, 2]], ref):
+        assert abs(e - r) <= 1e-6 * max(1.0, abs(r))
