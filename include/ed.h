@@ -25,6 +25,10 @@
  * data pointer); small outputs (dimensions, eigenvalues, info) are host memory.
  * `stream` is a hipStream_t passed as void* (NULL = the default stream).
  *
+ * Threads: a handle may be used by several host threads and streams at once (each
+ * call with vectors and a workspace of its own), except where a call says otherwise;
+ * it is freed once no call uses it.
+ *
  * Errors: every call returns an ed_status; nothing is thrown across this
  * interface.  The message of the last failure on the calling thread is returned
  * by ed_last_error().  ED_EINVAL: bad argument (detailed below per call);

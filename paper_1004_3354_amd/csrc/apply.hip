@@ -1905,8 +1905,10 @@ ApplyArgs<float, double> make_args<float, double>(const ed_ham_s *h, const void 
 
 template <class K>
 static void allow_lds(K kern) {
+    static std::mutex mu;  // handles of other threads launch the same kernels
     static std::vector<const void *> done;
     const void *f = (const void *)kern;
+    std::lock_guard<std::mutex> lk(mu);
     for (const void *d : done)
         if (d == f) return;
     (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 163840 - 8192);
@@ -2193,6 +2195,7 @@ void apply_launch_variant(ed_ham_s *h, int v, const void *x, void *y, hipStream_
     if (v < 0 || v >= kNumVariants) fail(ED_EINVAL, "apply variant %d out of range", v);
     const size_t elem = h->prec == ED_FP64 ? 8 : 4;
     if (!variant_fits(h, v, elem)) fail(ED_EINVAL, "apply variant %s does not apply to this Hamiltonian", kVariants[v].name);
+    std::lock_guard<std::mutex> lk(h->plan_mu);
     launch_store(h, v, x, y, s);
 }
 
@@ -2244,6 +2247,7 @@ static void tune(ed_ham_s *h, const void *x, void *y, hipStream_t s) {
 }
 
 void apply_launch(ed_ham_s *h, const void *x, void *y, hipStream_t s) {
+    std::lock_guard<std::mutex> lk(h->plan_mu);
     if (h->plan.variant < 0) tune(h, x, y, s);
     launch_store(h, h->plan.variant, x, y, s);
 }
@@ -2285,7 +2289,8 @@ static int64_t rayleigh_cap(const ed_ham_s *h) { return kDynBudget / (int64_t)(h
 
 // Number of (a, b) partial pairs the Rayleigh quotient writes, from the cached
 // window plan only (-1 when it is not there yet).
-int64_t rayleigh_pairs_cached(const ed_ham_s *h) {
+int64_t rayleigh_pairs_cached(ed_ham_s *h) {
+    std::lock_guard<std::mutex> lk(h->plan_mu);
     const int64_t cap = rayleigh_cap(h);
     for (size_t i = 0; i < h->windows.size(); ++i)
         if (h->windows[i].first == cap) return h->dup * (int64_t)h->window_counts[2 * i];
@@ -2295,6 +2300,7 @@ int64_t rayleigh_pairs_cached(const ed_ham_s *h) {
 // At handle creation: the window plan of the Rayleigh quotient and the LDS
 // attribute of its kernels, so that later calls allocate nothing for them.
 void prepare_rayleigh(ed_ham_s *h) {
+    std::lock_guard<std::mutex> lk(h->plan_mu);
     int nwin = 0, wmax = 0;
     (void)windows_for(h, rayleigh_cap(h), &nwin, &wmax);
     if (h->prec == ED_FP64) {
@@ -2315,7 +2321,10 @@ static void rayleigh_with(ed_ham_s *h, const void *x, double *part, int64_t nb, 
     double *out = part + 2 * nb;
     double hv[2];
     ApplyArgs<TX, double> a = make_args<TX, double>(h, x, nullptr, part, 0.0);
-    launch_rw<TX, double, 1, 512, 1, true>(h, a, s);
+    {
+        std::lock_guard<std::mutex> lk(h->plan_mu);
+        launch_rw<TX, double, 1, 512, 1, true>(h, a, s);
+    }
     k_sum_pairs<<<1, 256, 0, s>>>(part, nb, out);
     ED_LAUNCH_CHECK();
     ED_HIP(hipMemcpyAsync(hv, out, sizeof(hv), hipMemcpyDeviceToHost, s));
@@ -2323,7 +2332,10 @@ static void rayleigh_with(ed_ham_s *h, const void *x, double *part, int64_t nb, 
     if (!(hv[1] > 0.0)) fail(ED_EINVAL, "ed_rayleigh: zero vector");
     const double theta = hv[0] / hv[1];
     a.theta = theta;
-    launch_rw<TX, double, 1, 512, 2, true>(h, a, s);
+    {
+        std::lock_guard<std::mutex> lk(h->plan_mu);
+        launch_rw<TX, double, 1, 512, 2, true>(h, a, s);
+    }
     k_sum_pairs<<<1, 256, 0, s>>>(part, nb, out);
     ED_LAUNCH_CHECK();
     double r2[2];
@@ -2340,8 +2352,10 @@ void rayleigh_on(ed_ham_s *h, const void *x, double *part, int64_t nb, double *r
         rayleigh_with<float>(h, x, part, nb, rq, resid, s);
 }
 
-// The handle's own reduction buffer (grown on demand).
+// The handle's own reduction buffer (grown on demand), held until the result is on
+// the host: a second caller would overwrite the sums or free them.
 void rayleigh_fp64(ed_ham_s *h, const void *x, double *rq, double *resid, hipStream_t s) {
+    std::lock_guard<std::mutex> lk(h->red_mu);
     int64_t nb = rayleigh_pairs_cached(h);
     if (nb < 0) {
         prepare_rayleigh(h);
@@ -2384,7 +2398,11 @@ extern "C" int ed_apply_variant_fits(ed_ham_t h, int v) {
     return variant_fits(h, v, h->prec == ED_FP64 ? 8 : 4) ? 1 : 0;
 }
 
-extern "C" int ed_apply_current_variant(ed_ham_t h) { return h ? h->plan.variant : -1; }
+extern "C" int ed_apply_current_variant(ed_ham_t h) {
+    if (!h) return -1;
+    std::lock_guard<std::mutex> lk(h->plan_mu);
+    return h->plan.variant;
+}
 
 extern "C" ed_status ed_rayleigh(ed_ham_t h, const void *x, double *rq, double *resid, void *stream) {
     return guard([&] {

@@ -6,6 +6,7 @@
 #include <atomic>
 #include <cstdint>
 #include <cstring>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -224,6 +225,11 @@ struct ed_ham_s {
     // (source up rank, down move table, signed amplitude)
     ed::DevMem xl_off, xl_src, xl_tab, xl_amp64, xl_amp32;
     int xl_max = 0;             // largest list length
+    // A handle serves several host threads and streams at once.  plan_mu guards what
+    // its first calls fill in (plan, windows, items, tplans), held while a product is
+    // launched; red_mu guards redbuf, held until the Rayleigh quotient that uses it is
+    // done.  red_mu is taken before plan_mu.
+    std::mutex plan_mu, red_mu;
     ed::ApplyPlan plan;
     ed::DevMem redbuf;          // small FP64 reduction scratch owned by the handle
     size_t redbuf_doubles = 0;
@@ -333,7 +339,7 @@ int apply_variant_count(const ed_ham_s *h);
 const char *apply_variant_name(const ed_ham_s *h, int variant);
 void rayleigh_fp64(ed_ham_s *h, const void *x, double *rq, double *resid, hipStream_t s);
 void prepare_rayleigh(ed_ham_s *h);
-int64_t rayleigh_pairs_cached(const ed_ham_s *h);
+int64_t rayleigh_pairs_cached(ed_ham_s *h);
 void rayleigh_on(ed_ham_s *h, const void *x, double *part, int64_t nb, double *rq, double *resid, hipStream_t s);
 
 // Rank order <-> grouped order of a vector (layout.hip): dir 0 = to grouped.

@@ -363,3 +363,56 @@ def test_tridiagonal_lowest_eigenpair(m, reorth):
     if reorth == 3:
         gap = w[1] - w[0] if m > 1 else nrm
         assert abs(info["residual"] - abs(be[m - 1] * z[-1, 0])) <= 64 * eps * nrm / gap * be[m - 1]
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("name", ["aim8", "kan9"])
+def test_handle_shared_by_solves_and_rayleigh_quotients(name, prec):
+    """A new handle used by four threads at once, each on a stream of its own: two
+    solves with the FP64 Rayleigh quotient (refine), Rayleigh quotients of a given
+    vector, and products.  Everything equals the same call alone on that handle, so
+    neither the first calls' tuning and work lists nor the reduction buffer are
+    shared without order."""
+    import threading
+
+    ed = gpu_ed()
+    phys, nn = (wl.aim(7, 2.0, -1.0, seed=29), (4, 4)) if name == "aim8" else (wl.kanamori(3, 2, 2.3, 0.4, seed=3), (4, 5))
+    b, H = build(phys, *nn, prec)
+    v0, x = _v0(b.D, prec, 4), _v0(b.D, prec, 8)
+    ys = [torch.empty_like(x) for _ in range(5)]
+    o = ed.options(tol=1e-10 if prec == 0 else 1e-7, reorth=2, max_basis=30, keep=8, max_iter=3000, refine=1)
+    start, got, errs = threading.Barrier(4), [[] for _ in range(4)], []
+    torch.cuda.synchronize()
+
+    def work(t):
+        try:
+            with torch.cuda.stream(torch.cuda.Stream()):
+                start.wait(timeout=60)
+                for i in range(4):
+                    if t < 2:
+                        E, info = H.lanczos_ground(v0, o)
+                        got[t].append((E, info["residual"], info["rq_fp64"], info["iters"]))
+                    elif t == 2:
+                        got[t].extend(H.rayleigh(x) for _ in range(8))
+                    else:
+                        H.apply(x, ys[i])
+                torch.cuda.current_stream().synchronize()
+        except Exception as e:  # reported by the main thread
+            errs.append(e)
+
+    pool = [threading.Thread(target=work, args=(t,)) for t in range(4)]
+    for t in pool:
+        t.start()
+    for t in pool:
+        t.join()
+    assert not errs, errs
+    E, info = H.lanczos_ground(v0, o)
+    alone = (E, info["residual"], info["rq_fp64"], info["iters"])
+    assert got[0] == [alone] * 4 and got[1] == [alone] * 4
+    assert got[2] == [H.rayleigh(x)] * 32
+    H.apply(x, ys[4])
+    torch.cuda.synchronize()
+    for y in ys[:4]:
+        assert torch.equal(y, ys[4])
+    e_ref = orc.lowest_k(sector(phys, *nn), 1, tol=1e-13)[0]
+    assert _rel(E, e_ref) <= TOL[prec]
