@@ -648,6 +648,7 @@ __global__ __launch_bounds__(256) void kb_tridiag(BState st, BDims dm, double to
     double *alpha = st.alpha + (int64_t)s * dm.ms, *beta = st.beta + (int64_t)s * dm.ms;
     const double n2 = st.raw[(int64_t)s * dm.rs];
     const double bj = sqrt(n2);
+    __syncthreads();  // every wave has read the state that thread 0 moves on below
     if (threadIdx.x == 0) {
         beta[j] = bj;
         st.sig2[(int64_t)s * dm.ms + j + 1] = n2 > 0.0 ? 1.0 / n2 : 0.0;

@@ -268,3 +268,29 @@ def test_batched_sector_with_overflowing_coefficients(basis, keep):
     assert [i.converged for i in infos] == [1, 0, 1]
     for e, r in zip(E[[0, 2]], ref):
         assert abs(e - r) <= 1e-6 * max(1.0, abs(r))
+
+
+@pytest.mark.parametrize("max_iter", [4, 5, 6, 7])
+def test_batched_ends_between_two_checks(max_iter):
+    """A run that ends on a step without an eigensolve returns the Ritz pair of the
+    last one (four steps, check_every = 4) in every sector: the lowest eigenvalue of
+    the 4 x 4 tridiagonal matrix of the same start vector, whose Rayleigh quotient
+    agrees with it to the rounding of products and sums (64 eps of |H|)."""
+    ed = gpu_ed()
+    phys = wl.aim(7, 2.0, -1.0, seed=21)
+    secs = [(a, b) for a in range(3, 6) for b in range(3, 6)]
+    hs = _hams(phys, secs, 0)
+    v0s = []
+    for i, h in enumerate(hs):
+        v = torch.empty(h.D, dtype=torch.float64, device="cuda")
+        ed.fill_random(v, 60 + i, 1)
+        v0s.append(v)
+    E, info = ed.lanczos_ground_batched(hs * 8, ed.options(tol=1e-14, max_basis=40, max_iter=max_iter, check_every=4),
+                                        v0s=v0s * 8, allow_noconv=True)
+    for q in range(8 * len(secs)):
+        a, b, _ = hs[q % len(secs)].lanczos_tridiag(v0s[q % len(secs)], 4)
+        w = np.linalg.eigvalsh(np.diag(a) + np.diag(b[:3], 1) + np.diag(b[:3], -1))
+        nrm = np.max(np.abs(a)) + 2.0 * np.max(b)
+        assert info[q]["iters"] == max_iter and info[q]["converged"] == 0
+        assert abs(info[q]["ritz"] - w[0]) <= 64 * 2.0 ** -52 * nrm, (q, info[q]["ritz"], w[0])
+        assert abs(E[q] - w[0]) <= 64 * 2.0 ** -52 * nrm, (q, E[q], w[0])
