@@ -26,6 +26,7 @@
 #include <vector>
 
 #include "ed_internal.h"
+#include "sturm.h"
 
 namespace ed {
 
@@ -817,7 +818,7 @@ __global__ __launch_bounds__(256) void kb_plan(BState st, BDims dm, int keep, do
         for (int i = t; i < m; i += 256) {
             a[i] *= sc;
             b[i] = i < m - 1 ? b[i] * sc : 0.0;
-            b2[i] = b[i] * b[i];
+            b2[i] = sturm_b2(b[i]);
         }
         __syncthreads();
         auto bisect = [&](int n, int idx) {
@@ -866,7 +867,7 @@ __global__ __launch_bounds__(256) void kb_plan(BState st, BDims dm, int keep, do
             }
             __syncthreads();
         }
-        for (int i = t; i < keep; i += 256) b2[i] = i < keep - 1 ? b[i] * b[i] : 0.0;
+        for (int i = t; i + 1 < keep; i += 256) b2[i] = sturm_b2(b[i]);
         __syncthreads();
         if (t == 0) t0_s = bisect(keep, 0);
         __syncthreads();

@@ -34,6 +34,7 @@
 #include <cstdlib>
 
 #include "ed_internal.h"
+#include "sturm.h"
 
 namespace ed {
 
@@ -669,40 +670,6 @@ __global__ void k_finalize_norm(NormJob nj) {
     norm_job(nj, sh);
 }
 
-// Number of eigenvalues below x of the tridiagonal matrix with diagonal al and
-// squared off-diagonal b2, both scaled so that the matrix norm is about 1: sign
-// changes of the leading principal minors p_i = (al_i - x) p_{i-1} - b2_{i-1}
-// p_{i-2}, one dependent FMA per row (the ratio form q_i = p_i / p_{i-1} has a
-// division).  The pair is rescaled every four rows.  A zero minor counts by its
-// sign bit: its neighbours have opposite signs, so exactly one change is seen
-// whatever that bit is; a pair of zeros (x an eigenvalue of a decoupled leading
-// block) starts afresh.
-__device__ __forceinline__ int sturm_count(const double *al, const double *b2, int m, double x) {
-    double q = 1.0, p = al[0] - x;
-    int c = signbit(p) ? 1 : 0;
-    int i = 1;
-    for (; i + 4 <= m; i += 4) {
-#pragma unroll
-        for (int t = 0; t < 4; ++t) {
-            const double n = fma(al[i + t] - x, p, -(b2[i + t - 1] * q));
-            c += signbit(n) != signbit(p);
-            q = p;
-            p = n;
-        }
-        const double mx = fmax(fabs(p), fabs(q));
-        const double f = mx < 1e-120 ? 1e120 : (mx > 1e120 ? 1e-120 : 1.0);
-        p = mx == 0.0 ? 1.0 : p * f;
-        q *= f;
-    }
-    for (; i < m; ++i) {
-        const double n = fma(al[i] - x, p, -(b2[i - 1] * q));
-        c += signbit(n) != signbit(p);
-        q = p;
-        p = n;
-    }
-    return c;
-}
-
 // 1 / d to about an ulp for normal d (hardware reciprocal, two Newton steps): a
 // third of the dependent operations of a division.
 __device__ __forceinline__ double fast_rcp(double d) {
@@ -777,7 +744,7 @@ __device__ void k_tridiag_lowest_body(const double *alpha, const double *beta, i
         al[i] *= sc;
         const double b = be[i] * sc;
         be[i] = b;
-        b2[i] = b * b;
+        b2[i] = sturm_b2(b);
     }
     __syncthreads();
     for (int it = 0; it < 60; ++it) {
@@ -809,7 +776,7 @@ __device__ void k_tridiag_lowest_body(const double *alpha, const double *beta, i
         for (int i = 0; i < m - 1; ++i) {
             d = fabs(d) <= kTiny ? copysign(kTiny, d) : d;
             dp[i] = d;
-            d = fma(-b2[i], fast_rcp(d), al[i + 1]);
+            d = fma(-(be[i] * be[i]), fast_rcp(d), al[i + 1]);
         }
         dp[m - 1] = d;
     }
@@ -819,7 +786,7 @@ __device__ void k_tridiag_lowest_body(const double *alpha, const double *beta, i
         for (int i = m - 1; i > 0; --i) {
             e = fabs(e) <= kTiny ? copysign(kTiny, e) : e;
             em[i] = e;
-            e = fma(-b2[i - 1], fast_rcp(e), al[i - 1]);
+            e = fma(-(be[i - 1] * be[i - 1]), fast_rcp(e), al[i - 1]);
         }
         em[0] = e;
     }
