@@ -1351,65 +1351,85 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     for (int q = 0; q < nsec; ++q)
         if (act[q] < 0) fail(ED_EINVAL, "start vector of batched sector %d is zero or not finite", q);
 
-    // ---- tile schedule: time a few tile sizes on slot 0 -> slot 1 (every sector at step 0)
-    std::vector<int64_t> cands = {4096, 8192};
-    if (const char *env = std::getenv("ED_BATCH_TILE")) cands = {std::max<int64_t>(64, std::atoll(env))};
-    int64_t best_tile_size = 0;
-    float best_ms = 1e30f;
-    // row tiles (kb_tile) and the tiles of the sectors it does not take (kb_apply)
+    // ---- tile schedule: the row tiles (kb_tile) and the tiles of the sectors it does
+    // not take (kb_apply), each size picked by timing a few on slot 0 -> slot 1 (every
+    // sector at step 0); sizes that give the same list (rows longer than a tile) are
+    // timed once, a single list not at all.  kb_apply does best with few rows per tile:
+    // all sectors of a five-orbital N_s = 10 impurity (rows to 252 states, FP32, 48
+    // steps) 10.0, 11.1, 13.3 and 17.9 ms with 1024, 2048, 4096 and 8192 elements; at
+    // N_s = 15 (rows of 5005 and 6435 states, 16 steps) 156 ms with one row, 225 ms
+    // with five, 172 ms with twenty.
     struct Sched {
-        DevMem row, rest;
-        unsigned nrow = 0, nrest = 0;
-        size_t lrow = 0, lrest = 0;
+        DevMem mem;
+        unsigned n = 0;
+        size_t lds = 0;
+        int64_t tile = 0;
     };
-    std::unique_ptr<Sched> best;
-    hipEvent_t ev0, ev1;
-    ED_HIP(hipEventCreate(&ev0));
-    ED_HIP(hipEventCreate(&ev1));
     auto kern0 = kb_apply<TX, TX, 0>;
     auto kern1 = kb_tile<TX>;
     (void)hipFuncSetAttribute((const void *)kern0, hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
     (void)hipFuncSetAttribute((const void *)kern1, hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
     (void)hipGetLastError();
-    auto apply_step = [&](const Sched &q, hipStream_t cs) {
-        if (q.nrow)
-            kern1<<<q.nrow, kBBS, q.lrow, cs>>>(d_sec, q.row.template as<ATile>(), st.jcur, st.active);
-        if (q.nrest)
-            kern0<<<q.nrest, kBBS, q.lrest, cs>>>(d_sec, q.rest.template as<ATile>(), st.jcur, st.active, 0, nullptr);
+    auto launch = [&](const Sched &q, bool row, hipStream_t cs) {
+        if (!q.n) return;
+        if (row) kern1<<<q.n, kBBS, q.lds, cs>>>(d_sec, q.mem.template as<ATile>(), st.jcur, st.active);
+        else kern0<<<q.n, kBBS, q.lds, cs>>>(d_sec, q.mem.template as<ATile>(), st.jcur, st.active, 0, nullptr);
     };
-    for (int64_t tsz : cands) {
-        auto q = std::make_unique<Sched>();
-        const std::vector<ATile> tr = make_row_tiles(B, tsz, B.elem, &q->lrow);
-        const std::vector<ATile> ts = make_tiles(B, tsz, B.elem, true, &q->lrest);
-        q->nrow = (unsigned)tr.size();
-        q->nrest = (unsigned)ts.size();
-        q->row.alloc(tr.size() * sizeof(ATile));
-        q->rest.alloc(ts.size() * sizeof(ATile));
-        if (q->nrow) ED_HIP(hipMemcpyAsync(q->row.p, tr.data(), tr.size() * sizeof(ATile), hipMemcpyHostToDevice, s));
-        if (q->nrest) ED_HIP(hipMemcpyAsync(q->rest.p, ts.data(), ts.size() * sizeof(ATile), hipMemcpyHostToDevice, s));
-        apply_step(*q, s);
-        ED_HIP(hipEventRecord(ev0, s));
-        for (int r = 0; r < 3; ++r) apply_step(*q, s);
-        ED_HIP(hipEventRecord(ev1, s));
-        ED_LAUNCH_CHECK();
-        ED_HIP(hipEventSynchronize(ev1));
-        float ms = 0.f;
-        ED_HIP(hipEventElapsedTime(&ms, ev0, ev1));
-        if (ms < best_ms) {
-            best_ms = ms;
-            best = std::move(q);
-            best_tile_size = tsz;
+    struct Events {
+        hipEvent_t e[2] = {nullptr, nullptr};
+        ~Events() {
+            for (hipEvent_t v : e)
+                if (v) (void)hipEventDestroy(v);
         }
-    }
-    (void)hipEventDestroy(ev0);
-    (void)hipEventDestroy(ev1);
+    } ev;
+    for (hipEvent_t &e : ev.e) ED_HIP(hipEventCreate(&e));
+    auto choose = [&](bool row, std::vector<int64_t> cands) {
+        if (const char *env = std::getenv("ED_BATCH_TILE")) cands = {std::max<int64_t>(64, std::atoll(env))};
+        std::vector<std::unique_ptr<Sched>> qs;
+        std::vector<std::vector<ATile>> lists;
+        for (int64_t tsz : cands) {
+            auto q = std::make_unique<Sched>();
+            std::vector<ATile> t =
+                row ? make_row_tiles(B, tsz, B.elem, &q->lds) : make_tiles(B, tsz, B.elem, true, &q->lds);
+            if (!lists.empty() && lists.back().size() == t.size() &&
+                std::equal(t.begin(), t.end(), lists.back().begin(), [](const ATile &a, const ATile &b) {
+                    return a.sec == b.sec && a.u0 == b.u0 && a.nr == b.nr && a.lds == b.lds;
+                }))
+                continue;
+            q->n = (unsigned)t.size();
+            q->tile = tsz;
+            q->mem.alloc(t.size() * sizeof(ATile));
+            if (q->n) ED_HIP(hipMemcpyAsync(q->mem.p, t.data(), t.size() * sizeof(ATile), hipMemcpyHostToDevice, s));
+            qs.push_back(std::move(q));
+            lists.push_back(std::move(t));
+        }
+        size_t best = 0;
+        float best_ms = 1e30f;
+        for (size_t i = 0; qs.size() > 1 && i < qs.size(); ++i) {
+            launch(*qs[i], row, s);
+            ED_HIP(hipEventRecord(ev.e[0], s));
+            for (int r = 0; r < 3; ++r) launch(*qs[i], row, s);
+            ED_HIP(hipEventRecord(ev.e[1], s));
+            ED_LAUNCH_CHECK();
+            ED_HIP(hipEventSynchronize(ev.e[1]));
+            float ms = 0.f;
+            ED_HIP(hipEventElapsedTime(&ms, ev.e[0], ev.e[1]));
+            if (ms < best_ms) {
+                best_ms = ms;
+                best = i;
+            }
+        }
+        ED_HIP(hipStreamSynchronize(s));  // the lists' uploads, before they are released
+        return std::move(qs[best]);
+    };
+    const std::unique_ptr<Sched> rowq = choose(true, {4096, 8192}), restq = choose(false, {1024, 2048, 4096});
     // tiles of the final Rayleigh quotients, every sector
     DevMem tiles;
-    size_t best_lds = 0;
-    const std::vector<ATile> best_tiles = make_tiles(B, 2048, B.elem, false, &best_lds);
-    tiles.alloc(best_tiles.size() * sizeof(ATile));
-    ED_HIP(hipMemcpyAsync(tiles.p, best_tiles.data(), best_tiles.size() * sizeof(ATile), hipMemcpyHostToDevice, s));
-    const unsigned nt = (unsigned)best_tiles.size();
+    size_t rq_lds = 0;
+    const std::vector<ATile> rq_tiles = make_tiles(B, 2048, B.elem, false, &rq_lds);
+    tiles.alloc(rq_tiles.size() * sizeof(ATile));
+    ED_HIP(hipMemcpyAsync(tiles.p, rq_tiles.data(), rq_tiles.size() * sizeof(ATile), hipMemcpyHostToDevice, s));
+    const unsigned nt = (unsigned)rq_tiles.size();
     ED_HIP(hipStreamSynchronize(s));
 
     // ---- one step of every running sector, captured once
@@ -1419,7 +1439,8 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     if (o.keep > 0 && m > kPlanLds) plan_q.alloc(S * (size_t)m * (size_t)m * 8);
     const size_t plan_lds = o.keep > 0 && m <= kPlanLds ? (size_t)m * (size_t)m * 8 : 0;
     auto record_step = [&](hipStream_t cs) {
-        apply_step(*best, cs);
+        launch(*rowq, true, cs);
+        launch(*restq, false, cs);
         for (int ps = 0; ps < passes; ++ps) {
             // two passes: the first one on S_{j-1} and S_j only, the vectors on
             // which H S_j has a component by the recurrence; a first pass over the
@@ -1484,10 +1505,10 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
         auto kern = kb_apply<TX, double, 1>;
         (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
         (void)hipGetLastError();
-        kern<<<nt, kBBS, best_lds, s>>>(d_sec64, tiles.as<ATile>(), st.jcur, st.active, 0, tp.as<double>());
+        kern<<<nt, kBBS, rq_lds, s>>>(d_sec64, tiles.as<ATile>(), st.jcur, st.active, 0, tp.as<double>());
         std::vector<int> tfc((size_t)2 * nsec, 0);  // first tile, tile count per sector
-        for (size_t t = 0; t < best_tiles.size(); ++t) {
-            const int q = best_tiles[t].sec;
+        for (size_t t = 0; t < rq_tiles.size(); ++t) {
+            const int q = rq_tiles[t].sec;
             if (tfc[(size_t)nsec + q] == 0) tfc[q] = (int)t;
             ++tfc[(size_t)nsec + q];
         }
@@ -1531,7 +1552,7 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
             info[q] = f;
         }
     }
-    g_last.tile = best_tiles.empty() ? 0 : best_tile_size;
+    g_last.tile = rowq->n ? rowq->tile : restq->tile;
     g_last.steps = launches;
     g_last.restart_events = evs[0];
     g_last.bytes = bytes;

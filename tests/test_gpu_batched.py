@@ -294,3 +294,36 @@ def test_batched_ends_between_two_checks(max_iter):
         assert info[q]["iters"] == max_iter and info[q]["converged"] == 0
         assert abs(info[q]["ritz"] - w[0]) <= 64 * 2.0 ** -52 * nrm, (q, info[q]["ritz"], w[0])
         assert abs(E[q] - w[0]) <= 64 * 2.0 ** -52 * nrm, (q, E[q], w[0])
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("tile", [0, 64, 1024, 4096, 32768])
+@pytest.mark.parametrize("name", ["m5", "ns15"])
+def test_batched_sectors_without_row_tiles(name, tile, prec, monkeypatch):
+    """Sectors the row tiles do not take: five sites in the cross term (rows of 1 to
+    252 states), and rows too long for LDS (N_s = 15, 5005 and 6435 states) next to
+    sectors that have row tiles; one row, several rows and a whole sector per tile
+    (tile 0: picked by timing).  Against the oracle's lowest levels."""
+    ed = gpu_ed()
+    if tile:
+        monkeypatch.setenv("ED_BATCH_TILE", str(tile))
+    if name == "m5":
+        phys, secs = wl.kanamori(5, 1, 2.3, 0.4, seed=3), [(0, 0), (10, 4), (1, 5), (3, 2), (5, 1), (2, 5), (4, 4)]
+    else:
+        phys, secs = wl.kanamori(3, 4, 2.3, 0.4, seed=3), [(1, 7), (0, 8), (2, 2), (14, 6), (15, 9), (1, 1)]
+    E, info = ed.lanczos_ground_batched(_hams(phys, secs, prec), ed.options(
+        tol=1e-10 if prec == 0 else 1e-7, max_basis=60, reorth=2, max_iter=2000), seed=3)
+    for e, i, s in zip(E, info, secs):
+        ref = _lowest(name, s, phys)
+        assert i["converged"] == 1, (s, i)
+        assert abs(e - ref) <= (1e-10 if prec == 0 else 1e-6) * max(1.0, abs(ref)), (name, s, e, ref)
+
+
+_LOWEST = {}
+
+
+def _lowest(name, s, phys):
+    import oracle as orc
+    if (name, s) not in _LOWEST:
+        _LOWEST[name, s] = orc.lowest_k(orc.sector_for(phys, *s), 1, tol=1e-13)[0]
+    return _LOWEST[name, s]
