@@ -72,7 +72,9 @@ struct RChunk {
 
 // Per-sector state.  Strides: ms = m + 2 (sig2, gamma, alpha, beta), mt = m + 8
 // (tri: theta, residual, beta_last, eigenvector), rs = 2 m + 4 (raw sums), mg =
-// (m + 1)^2 (Gram matrix), mc = (m + 1) * max(1, keep + 1) (restart coefficients).
+// (m + 1)^2 (Gram matrix, reorth = 3; a restart plan of more than kPlanLds vectors
+// takes its place once the basis it belongs to is full, and m^2 without one),
+// mc = (m + 1) * max(1, keep + 1) (restart coefficients).
 struct BState {
     double *sig2, *gamma, *alpha, *beta, *tri, *raw, *gram, *coef, *a2b2;
     double *theta, *resid;
@@ -97,6 +99,7 @@ static constexpr int kBBS = 256;
 static constexpr int kBatchBasisDefault = 60;  // basis per sector when max_basis = 0
 static constexpr int kBChunk = 8192;           // elements per vector-kernel workgroup
 static constexpr int kBRMaxC = 4400;           // restart coefficients held in LDS (nin * NO)
+static constexpr int kPlanLds = 80;            // basis size up to which a restart plan's Q is in LDS
 
 // Window of stored vectors a pass projects against: all of S_0..S_j, or
 // S_{j-1}, S_j for the plain three-term recurrence (reorth = 0) and the first of
@@ -775,9 +778,8 @@ __global__ __launch_bounds__(kBBS) void kb_restart_v4(const BSec<TX, TX> *secs, 
 // of the rotations' chain, about 40 us for m = 20, keep = 8; the same plans on the
 // host (16 threads, up to a hundred waiting sectors, their states copied there and
 // back) left the GPU idle for 0.1 ms per step on average.  Q in LDS for m <=
-// kPlanLds, else in qg.
-static constexpr int kPlanLds = 80;
-__global__ __launch_bounds__(256) void kb_plan(BState st, BDims dm, int keep, double *qg) {
+// kPlanLds, else in the sector's Gram matrix, which the restart resets.
+__global__ __launch_bounds__(256) void kb_plan(BState st, BDims dm, int keep) {
     const int s = blockIdx.x;
     if (st.active[s] != 2) return;
     extern __shared__ __align__(16) unsigned char smem_raw[];
@@ -832,7 +834,7 @@ __global__ __launch_bounds__(256) void kb_plan(BState st, BDims dm, int keep, do
             return 0.5 * (l + h);
         };
         for (int i = t; i < m; i += 256) ev[i] = bisect(m, i);
-        double *Q = m <= kPlanLds ? reinterpret_cast<double *>(smem_raw) : qg + (int64_t)s * m * m;  // [col][row]
+        double *Q = m <= kPlanLds ? reinterpret_cast<double *>(smem_raw) : st.gram + (int64_t)s * dm.mg;  // [col][row]
         for (int i = t; i < m * m; i += 256) Q[i] = i % (m + 1) == 0 ? 1.0 : 0.0;
         __syncthreads();
         for (int e = keep; e < m; ++e) {
@@ -1049,7 +1051,8 @@ static void batch_dims(Batch &B, const ed_lanczos_opts &o) {
     d.ms = d.m + 2;
     d.mt = d.m + 8;
     d.rs = 2 * d.m + 4;
-    d.mg = o.reorth == 3 ? (int64_t)(d.m + 1) * (d.m + 1) : 0;
+    d.mg = o.reorth == 3 ? (int64_t)(d.m + 1) * (d.m + 1)
+                         : (o.keep > 0 && d.m > kPlanLds ? (int64_t)d.m * d.m : 0);
     d.mc = (d.m + 1) * std::max(1, o.keep + 1);
     d.reorth = o.reorth;
     d.check = std::max(1, o.check_every);
@@ -1435,8 +1438,6 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
     // ---- one step of every running sector, captured once
     const int passes = o.reorth == 2 ? 2 : 1;
     const unsigned prow = (unsigned)(o.reorth == 3 ? 2 * (m + 1) : m + 1);
-    DevMem plan_q;
-    if (o.keep > 0 && m > kPlanLds) plan_q.alloc(S * (size_t)m * (size_t)m * 8);
     const size_t plan_lds = o.keep > 0 && m <= kPlanLds ? (size_t)m * (size_t)m * 8 : 0;
     auto record_step = [&](hipStream_t cs) {
         launch(*rowq, true, cs);
@@ -1457,7 +1458,7 @@ static ed_status run_batched(int nsec, const ed_ham_t *hs, const ed_lanczos_opts
         kb_rowsum<TX><<<dim3(1, (unsigned)nsec), 64, 0, cs>>>(d_sec, st, dm, 1, part);
         kb_tridiag<<<nsec, 256, 0, cs>>>(st, dm, o.tol);
         // sectors whose basis is full restart
-        kb_plan<<<nsec, 256, plan_lds, cs>>>(st, dm, o.keep, plan_q.as<double>());
+        kb_plan<<<nsec, 256, plan_lds, cs>>>(st, dm, o.keep);
         combine(o.keep > 0 ? o.keep + 1 : 1, cs);
     };
     hipStream_t cs;

@@ -327,3 +327,34 @@ def _lowest(name, s, phys):
     if (name, s) not in _LOWEST:
         _LOWEST[name, s] = orc.lowest_k(orc.sector_for(phys, *s), 1, tol=1e-13)[0]
     return _LOWEST[name, s]
+
+
+@pytest.mark.parametrize("basis,reorth", [(81, 2), (81, 3), (100, 1), (100, 3)])
+def test_batched_restart_plans_stay_in_the_workspace(basis, reorth):
+    """Restart plans of more than 80 vectors: their matrices are part of the reported
+    workspace (without a Gram matrix they add m * m doubles per sector), nothing is
+    written behind it, and sectors that restarted reach the oracle's energies."""
+    import ctypes
+
+    ed = gpu_ed()
+    phys, secs = wl.kanamori(3, 2, 2.3, 0.4, seed=3), [(4, 5), (4, 4), (3, 5)]
+    hs = _hams(phys, secs, 0)
+    handles = ctypes.cast((ctypes.c_void_p * 3)(*[h._h for h in hs]), ctypes.c_void_p)
+
+    def query(keep):
+        n = ctypes.c_size_t()
+        o = ed.options(max_basis=basis, keep=keep, reorth=reorth)
+        assert ed._lib.ed_batched_workspace_bytes(3, handles, ctypes.byref(o), ctypes.byref(n)) == ed.ED_OK
+        return n.value
+
+    if reorth != 3:
+        assert query(8) - query(0) >= 3 * basis * basis * 8
+    n = query(8)
+    buf = torch.full((n + 65536,), 0xA5, dtype=torch.uint8, device="cuda")
+    E, info = ed.lanczos_ground_batched(hs, ed.options(tol=1e-15, max_basis=basis, keep=8, reorth=reorth, max_iter=240),
+                                        seed=7, ws=buf[:n], allow_noconv=True)
+    assert bool((buf[n:] == 0xA5).all())
+    assert any(i["restarts"] > 0 for i in info)
+    for e, s in zip(E, secs):
+        ref = _lowest("kan9", s, phys)
+        assert abs(e - ref) <= 1e-10 * max(1.0, abs(ref)), (s, e, ref)
