@@ -1545,15 +1545,14 @@ static const int2 *windows_for(ed_ham_s *h, int64_t cap, int *nwin, int *wmax) {
                                      : plan_windows(h->dn_states_host, h->ns, cap);
     int mx = 0;
     for (auto &v : w) mx = std::max(mx, v.y);
-    DevMem *m = new DevMem();
-    m->alloc(w.size() * sizeof(int2));
-    ED_HIP(hipMemcpy(m->p, w.data(), w.size() * sizeof(int2), hipMemcpyHostToDevice));
-    h->windows.push_back({cap, m});
+    auto m = device_copy(w);
+    h->windows.push_back({cap, m.get()});
+    const int2 *win = m.release()->as<int2>();
     h->window_counts.push_back((int)w.size());
     h->window_counts.push_back(mx);
     *nwin = (int)w.size();
     *wmax = mx;
-    return m->as<int2>();
+    return win;
 }
 
 // Work list of a grouped schedule over column ranges `cols` (windows or
@@ -1601,13 +1600,12 @@ static const int4 *items_for(ed_ham_s *h, int64_t key, const std::vector<int64_t
     std::vector<int4> out(len * kX, make_int4(0, 0, 0, 0));
     for (int x = 0; x < kX; ++x)
         for (size_t i = 0; i < run[x].size(); ++i) out[x + kX * i] = run[x][i];
-    DevMem *m = new DevMem();
-    m->alloc(out.size() * sizeof(int4));
-    ED_HIP(hipMemcpy(m->p, out.data(), out.size() * sizeof(int4), hipMemcpyHostToDevice));
-    h->items.push_back({key, m});
+    auto m = device_copy(out);
+    h->items.push_back({key, m.get()});
+    const int4 *list = m.release()->as<int4>();
     h->item_counts.push_back((int64_t)out.size());
     *count = (int64_t)out.size();
-    return m->as<int4>();
+    return list;
 }
 
 // Largest down component of a grouped handle.

@@ -6,6 +6,7 @@
 #include <atomic>
 #include <cstdint>
 #include <cstring>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -86,6 +87,15 @@ struct DevMem {
     }
     template <class T> T *as() const { return static_cast<T *>(p); }
 };
+
+// Device copy of a host list; nothing is left behind when it does not fit.
+template <class T>
+std::unique_ptr<DevMem> device_copy(const std::vector<T> &v) {
+    auto m = std::make_unique<DevMem>();
+    m->alloc(v.size() * sizeof(T));
+    ED_HIP(hipMemcpy(m->p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
+    return m;
+}
 
 inline unsigned grid_for(int64_t n, int block, int64_t cap = 1 << 20) {
     int64_t g = (n + block - 1) / block;
