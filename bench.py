@@ -260,7 +260,7 @@ def time_to_e0(cfg, precs, max_basis, tol, seed_idx, reorth=3, keep=0):
         torch.cuda.empty_cache()
     out["max_basis"] = max_basis
     out["tol"] = tol
-    out["reorth"] = {2: "CGS2, the first pass on the two vectors of the recurrence", 3: "both CGS2 projections from one read of the basis"}.get(reorth, reorth)
+    out["reorth"] = {2: "two passes, the first on the two vectors of the recurrence", 3: "two full projections from one read of the basis"}.get(reorth, reorth)
     if "fp64" in out and "fp32_mixed" in out:
         e64 = out["fp64"]["E0"]
         out["fp32_vs_fp64_rel"] = abs(out["fp32_mixed"]["E0"] - e64) / max(1.0, abs(e64))
@@ -392,7 +392,7 @@ def batched_bench():
     """All 169 sectors of the N_s = 12 three-orbital impurity: the batched
     FP32-mixed Lanczos (graph-replayed steps, per-sector restarts), in the
     tuned setting (20 stored vectors keeping 8, both projections per basis read)
-    and in the plain one (60 vectors, CGS2, explicit restarts), vs the same
+    and in the plain one (60 vectors, reorth = 2, explicit restarts), vs the same
     sectors solved one after another by the single-sector solver."""
     import numpy as np
     import torch

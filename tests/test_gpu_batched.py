@@ -358,3 +358,34 @@ def test_batched_restart_plans_stay_in_the_workspace(basis, reorth):
     for e, s in zip(E, secs):
         ref = _lowest("kan9", s, phys)
         assert abs(e - ref) <= 1e-10 * max(1.0, abs(ref)), (s, e, ref)
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("reorth", [2, 3])
+def test_batched_basis_is_orthogonal(reorth, prec):
+    """max |<v_i, v_j>| of the vectors that the batch's first sector leaves in the
+    workspace: each is rounded when it is stored (twice for reorth = 2, once per
+    pass, u each), and the FP64 sums leave 64 eps of |H v| over the smallest beta."""
+    ed = gpu_ed()
+    phys, secs = wl.kanamori(3, 2, 2.3, 0.4, seed=3), [(4, 5), (4, 4)]
+    hs = _hams(phys, secs, prec)
+    D, (dt, elem) = hs[0].D, ((torch.float64, 8), (torch.float32, 4))[prec]
+    ws = torch.zeros(1 << 27, dtype=torch.uint8, device="cuda")
+    # one step short of the basis: no restart, and S_0 alone is overwritten by the Ritz vector
+    _, info = ed.lanczos_ground_batched(hs, ed.options(tol=1e-15, max_basis=50, reorth=reorth, max_iter=49), seed=3,
+                                        ws=ws, allow_noconv=True)
+    n = info[0]["iters"]
+    assert info[0]["restarts"] == 0 and n == 49
+    S = [ws[i * D * elem:(i + 1) * D * elem].view(dt) for i in range(1, n + 1)]
+    y = torch.empty(D, dtype=dt, device="cuda")
+    hv = 0.0
+    for v in S[:-1]:
+        hs[0].apply(v.clone(), y)
+        hv = max(hv, float(y.double().norm() / v.double().norm()))
+    V = torch.stack([v.double() for v in S])
+    beta = float(V.norm(dim=1).min())
+    V /= V.norm(dim=1, keepdim=True)
+    unit = 2.0 ** -53 if prec == 0 else 2.0 ** -24
+    worst = float((V @ V.T).abs().fill_diagonal_(0.0).max())
+    print("orthogonality %.2e" % worst)
+    assert worst <= 2 * unit + 64 * 2.0 ** -52 * hv / beta

@@ -416,3 +416,42 @@ def test_handle_shared_by_solves_and_rayleigh_quotients(name, prec):
         assert torch.equal(y, ys[4])
     e_ref = orc.lowest_k(sector(phys, *nn), 1, tol=1e-13)[0]
     assert _rel(E, e_ref) <= TOL[prec]
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("name,k,tol,reorth,basis,keep", [
+    ("aim8", 1, 1e-10, 2, 120, 0), ("aim8", 1, 1e-10, 3, 120, 0), ("aim8", 5, 1e-3, 2, 120, 0),
+    ("kan9", 1, 1e-10, 2, 24, 8), ("kan9", 1, 1e-10, 3, 24, 8), ("kan9", 6, 1e-4, 2, 20, 6), ("hub6", 3, 1e-10, 2, 120, 0),
+], ids=["two", "gram", "two-locked", "two-restarts", "gram-restarts", "two-locked-restarts", "two-small"])
+def test_device_basis_is_orthogonal(name, k, tol, reorth, basis, keep, prec):
+    """max |<v_i, v_j>| of the stored vectors that a solve leaves in its workspace, and
+    against the locked ones (some locked at a loose tolerance, so that the products
+    have a component on them).  A vector is rounded once when it is stored and once
+    more when a restart combines it (2 u each, u the unit roundoff of the storage), and
+    the FP64 sums leave 64 eps of |H v| over the smallest beta.  reorth = 2 projects
+    once on two vectors and once on all, reorth = 3 twice on all."""
+    ed = gpu_ed()
+    phys, nn = {"aim8": (wl.aim(7, 2.0, -1.0, seed=5), (4, 4)), "kan9": (wl.kanamori(3, 2, 2.3, 0.4, seed=3), (4, 5)),
+                "hub6": (wl.hubbard(3, 2, 1.0, 4.0), (3, 3))}[name]
+    b, H = build(phys, *nn, prec)
+    o = ed.options(tol=tol if prec == 0 else max(tol, 1e-7), reorth=reorth, max_basis=basis, keep=keep, max_iter=3000,
+                   layout=1)
+    dt, elem = (torch.float64, 8) if prec == 0 else (torch.float32, 4)
+    ws = torch.zeros(H.workspace_bytes(o, k), dtype=torch.uint8, device=DEV)
+    _, info = H.lowest(k, _v0(b.D, prec, 5), o, ws=ws)
+    steps, restarts = info[-1]["iters"], info[-1]["restarts"]
+    assert (restarts > 0) == (keep > 0)
+    last = keep + steps - basis - (restarts - 1) * (basis - keep) if restarts else steps   # S_0 .. S_last
+    size = (b.D * elem + 255) // 256 * 256   # slots of the basis, then of the locked vectors
+    S = [ws[i * size:i * size + b.D * elem].view(dt) for i in list(range(last + 1)) + [basis + 1 + e for e in range(k - 1)]]
+    y = torch.empty(b.D, dtype=dt, device=DEV)
+    hv = 0.0
+    for v in S[:last]:
+        H.apply(v.clone(), y)
+        hv = max(hv, float(y.double().norm() / v.double().norm()))
+    beta = min(float(v.double().norm()) for v in S[(keep if restarts else 0) + 1:last + 1])
+    V = torch.stack([v.double() for v in S])
+    V /= V.norm(dim=1, keepdim=True)
+    G = (V @ V.T).abs().fill_diagonal_(0.0)
+    unit = 2.0 ** -53 if prec == 0 else 2.0 ** -24
+    assert float(G[:last + 1].max()) <= 4 * unit + 64 * 2.0 ** -52 * hv / beta
