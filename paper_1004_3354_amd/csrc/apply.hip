@@ -1903,10 +1903,8 @@ ApplyArgs<float, double> make_args<float, double>(const ed_ham_s *h, const void 
 
 template <class K>
 static void allow_lds(K kern) {
-    static std::mutex mu;  // handles of other threads launch the same kernels
-    static std::vector<const void *> done;
+    thread_local std::vector<const void *> done;  // of this thread: handles of others launch the same kernels
     const void *f = (const void *)kern;
-    std::lock_guard<std::mutex> lk(mu);
     for (const void *d : done)
         if (d == f) return;
     (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 163840 - 8192);
