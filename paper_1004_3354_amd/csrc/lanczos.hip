@@ -43,9 +43,20 @@ static constexpr int kMaxVec = 1024;  // locked + stored basis vectors per kerne
 static constexpr int kIRMaxIn = 257;  // implicit restart: at most 256 basis vectors + the residual
 static constexpr int kIRMaxOut = 17;  // and at most 16 kept vectors + the new residual
 
-// Workgroups (= partial sums per vector) of the dot kernels: 1024 elements each
-// (one group of four per thread), at most 2048 workgroups.
-int reduce_blocks(int64_t n) { return (int)std::min<int64_t>(std::max<int64_t>((n + 1023) / 1024, 1), 2048); }
+// Workgroups of `per` elements each, at most 2048.  Where one pass of 2048 workgroups
+// does not cover n, up to four passes are made whole (per a multiple): 2048 equal
+// shares of D = 2.9e6 are 1.4 passes of 1024 elements, the second half empty (60
+// steps of reorth = 3, FP32: 11.6 ms, with whole passes 10.5); beyond four it no
+// longer shows.
+static int blocks_of(int64_t n, int64_t per) {
+    n = std::max<int64_t>(n, 1);
+    if (n <= 4 * 2048 * 1024) per *= (n + 2048 * per - 1) / (2048 * per);
+    return (int)std::min<int64_t>((n + per - 1) / per, 2048);
+}
+
+// Workgroups (= partial sums per vector) of the dot kernels: 1024 elements a pass
+// (one group of four per thread).
+int reduce_blocks(int64_t n) { return blocks_of(n, 1024); }
 
 // The update kernel splits the vectors of a sum over a workgroup's four waves
 // for n up to this (256 elements per workgroup): at D = 4900 with 36 vectors
@@ -53,8 +64,7 @@ int reduce_blocks(int64_t n) { return (int)std::min<int64_t>(std::max<int64_t>((
 // elements per workgroup, and there are workgroups enough.
 static constexpr int64_t kSplitMax = 131072;
 static int update_blocks(int64_t n) {
-    const int64_t per = n <= kSplitMax ? 256 : 1024;
-    return (int)std::min<int64_t>(std::max<int64_t>((n + per - 1) / per, 1), 2048);
+    return blocks_of(n, n <= kSplitMax ? 256 : 1024);
 }
 
 // contiguous element range of block `blk` out of `nblk`
@@ -196,9 +206,12 @@ struct LocalPass {
 };
 
 // One group of dots over the elements [a, b): vectors vecs[g0 .. g0 + cnt), cnt <=
-// G (G a multiple of 4, the unused ones repeat the group's first vector and are
-// not written), all G loads in flight.
-template <typename TX, int G, bool TWO>
+// G, all loads in flight.  The unused places are skipped (SKIP: the branches also
+// take 14 registers off the two-sided FP64 form of eight vectors; N_s = 15 FP64,
+// reorth = 3, 24 vectors keeping 8, 80 steps 225.3 -> 221.1 ms) or repeat the group's
+// first vector (branches in a loop of 16 put its array in scratch); either way they
+// are not written.
+template <typename TX, int G, bool TWO, bool SKIP>
 __device__ __forceinline__ void dots_group(const TX *const *vecs, int g0, int cnt, int nvec, const TX *y, const TX *z,
                                            int64_t a, int64_t b, double *partials, int nblk, int blk,
                                            double (*red)[kRedBS / 64][16]) {
@@ -216,14 +229,17 @@ __device__ __forceinline__ void dots_group(const TX *const *vecs, int g0, int cn
         if constexpr (TWO) zv = load4(z + k);
         Q4<TX> sv[G];
 #pragma unroll
-        for (int i = 0; i < G; ++i) sv[i] = load4(vp[i] + k);
-#pragma unroll
         for (int i = 0; i < G; ++i)
+            if (!SKIP || i < cnt) sv[i] = load4(vp[i] + k);
+#pragma unroll
+        for (int i = 0; i < G; ++i) {
+            if (SKIP && i >= cnt) break;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 ay[i] += (double)sv[i].v[e] * (double)yv.v[e];
                 if constexpr (TWO) az[i] += (double)sv[i].v[e] * (double)zv.v[e];
             }
+        }
     }
     for (int64_t e = k; e < b && e < k + 4; ++e) {  // ragged end of the block
 #pragma unroll
@@ -252,10 +268,10 @@ __device__ __forceinline__ void dots_group(const TX *const *vecs, int g0, int cn
 }
 
 // partials[v * nblk + blk] = sum S_v Y; TWO: also sum S_v Z at
-// partials[(nvec + v) * nblk + blk].  The vectors go in groups of gs (<= GM, a
-// multiple of 4, or 2); blockIdx.y strides over the groups (one group per
-// workgroup for a small sector, whose workgroups would otherwise be too few).
-// HBM bound for large n; for a small one, by the chain of dependent loads.
+// partials[(nvec + v) * nblk + blk].  The vectors go in groups of gs <= GM;
+// blockIdx.y strides over the groups (one group per workgroup for a small sector,
+// whose workgroups would otherwise be too few).  HBM bound for large n; for a small
+// one, by the chain of dependent loads.
 template <typename TX, int GM, bool TWO>
 __global__ __launch_bounds__(kRedBS) void k_dots(const TX *const *vecs, int nvec, int gs, const TX *y, const TX *z,
                                                  int64_t n, double *partials, NormJob nj) {
@@ -267,15 +283,13 @@ __global__ __launch_bounds__(kRedBS) void k_dots(const TX *const *vecs, int nvec
     block_range(n, nblk, blk, a, b);
     for (int g0 = gs * (int)blockIdx.y; g0 < nvec; g0 += gs * (int)gridDim.y) {
         const int cnt = min(gs, nvec - g0);
-        if constexpr (GM == 2) {
-            dots_group<TX, 2, TWO>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
+        if constexpr (GM <= 8) {
+            dots_group<TX, GM, TWO, GM == 8>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
         } else {
-            if (cnt <= 4) dots_group<TX, 4, TWO>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
-            else if (cnt <= 8) dots_group<TX, 8, TWO>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
-            else if constexpr (GM > 8) {
-                if (cnt <= 12) dots_group<TX, 12, TWO>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
-                else dots_group<TX, 16, TWO>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
-            }
+            if (cnt <= 4) dots_group<TX, 4, TWO, false>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
+            else if (cnt <= 8) dots_group<TX, 8, TWO, false>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
+            else if (cnt <= 12) dots_group<TX, 12, TWO, false>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
+            else dots_group<TX, 16, TWO, false>(vecs, g0, cnt, nvec, y, z, a, b, partials, nblk, blk, red);
         }
     }
 }
@@ -1232,13 +1246,16 @@ struct Solver {
 
     template <typename TX, int GM, bool TWO>
     void launch_dots(int vbeg, int nvec, const void *y, const void *z, double *out) {
-        // groups of about equal size (Y is read once per group)
+        // groups of 16: of about equal size, multiples of 4 (Y is read once per group)
         const int ng = (nvec + GM - 1) / GM;
-        const int gs = GM == 2 ? 2 : std::min(GM, ((nvec + ng - 1) / ng + 3) & ~3);
-        // a workgroup per group while the element ranges alone are too few to
-        // fill the chip; large sectors loop over the groups inside, so that a
-        // range's Y comes from the caches for the second group on
-        const unsigned gy = w.nblk < 2048 ? (unsigned)((nvec + gs - 1) / gs) : 1u;
+        const int gs = GM <= 8 ? GM : std::min(GM, ((nvec + ng - 1) / ng + 3) & ~3);
+        // a workgroup per group while the element ranges alone are too few to fill the
+        // chip, and up to 32 MiB a vector, where Y comes from the Infinity Cache for
+        // every group (60 steps of reorth = 3 at D = 2.3e6, FP64: 16.3 -> 15.3 ms, at
+        // 6.8e6 44.0 -> 45.8); larger sectors loop over the groups inside, so that a
+        // range's Y is near for the second group on
+        const bool spread = w.nblk < 2048 && (size_t)h->D * sizeof(TX) <= (size_t)32 << 20;
+        const unsigned gy = spread ? (unsigned)((nvec + gs - 1) / gs) : 1u;
         k_dots<TX, GM, TWO><<<dim3((unsigned)w.nblk, gy), kRedBS, 0, s>>>(
             (const TX *const *)(w.vp + vbeg), nvec, gs, (const TX *)y, (const TX *)z, h->D, out, take_norm());
         ED_LAUNCH_CHECK();
@@ -1253,8 +1270,14 @@ struct Solver {
                 return;
             }
         }
-        // FP64 keeps to 8 vectors (registers)
+        // FP64 keeps to 8 vectors (registers).  FP32: 16 leave one wave per SIMD (256
+        // registers), which reads Y half as often and wins once the vectors come from
+        // HBM; up to 2^24 elements, where the Infinity Cache still holds several, 8 and
+        // three waves do.  reorth = 3 with 30 vectors keeping 8, 80 steps, 8 against 16:
+        // D = 853,776 6.2 and 7.7 ms, 2.9e6 12.2 and 15.0, 1.5e7 46.9 and 48.8, 3.2e7
+        // 90.8 and 89.4, 4.1e7 125.5 and 121.7.
         if (f64) launch_dots<double, 8, TWO>(vbeg, nvec, y, z, out);
+        else if (h->D <= (int64_t)1 << 24) launch_dots<float, 8, TWO>(vbeg, nvec, y, z, out);
         else launch_dots<float, 16, TWO>(vbeg, nvec, y, z, out);
     }
     template <typename TX>
@@ -1317,7 +1340,16 @@ struct Solver {
         } else {
             count(nloc + 1);
             run_dots<false>(vl, nloc, Y, nullptr, w.locpart);
-            if (o.reorth == 0) {  // three-term recurrence: nothing more to project on
+            if (o.reorth == 0 && w.nblk > 1024) {  // three-term recurrence: nothing more to project on
+                count(nloc + 2);
+                k_finalize_dots_par<<<nloc, 256, 0, s>>>(w.locpart, w.nblk, w.sig2 + vl, nullptr, w.gamma + vl, al,
+                                                         nloc - 1, nullptr, 0);
+                ED_LAUNCH_CHECK();
+                lincomb_any(vl, w.gamma + vl, DirectCoef{}, nloc, Y, 0, 1.0, w.npart, post);
+            } else if (o.reorth == 0) {
+                // every workgroup sums the partials itself: a launch less, but more than
+                // it costs once there are over 1024 of them (60 steps at D = 2.3e6,
+                // FP32: 2.72 against 2.57 ms)
                 count(nloc + 2);
                 lincomb_any(vl, nullptr, DirectCoef{w.locpart, w.nblk, w.sig2 + vl, nullptr, 0, al}, nloc, Y, 0, 1.0,
                             w.npart, post);

@@ -455,3 +455,44 @@ def test_device_basis_is_orthogonal(name, k, tol, reorth, basis, keep, prec):
     G = (V @ V.T).abs().fill_diagonal_(0.0)
     unit = 2.0 ** -53 if prec == 0 else 2.0 ** -24
     assert float(G[:last + 1].max()) <= 4 * unit + 64 * 2.0 ** -52 * hv / beta
+
+
+@pytest.mark.parametrize("prec", [0, 1], ids=["fp64", "fp32"])
+@pytest.mark.parametrize("reorth", [0, 1, 2, 3])
+@pytest.mark.parametrize("nn", [(3, 6), (4, 6), (4, 7), (5, 7)], ids=["2.3e6", "6.8e6", "8.8e6", "1.9e7"])
+def test_step_relation_where_the_vector_kernels_split(nn, reorth, prec):
+    """Every step obeys H v_j = beta_{j-1} v_{j-1} + alpha_j v_j + beta_j v_{j+1} on the
+    stored vectors, and they are orthogonal, at sizes on both sides of the vector
+    kernels' rules: two and four whole passes of the workgroups and beyond (8.4e6),
+    groups of vectors side by side or in turn (32 MiB a vector), 8 or 16 vectors per
+    group (1.7e7 FP32), partial sums finished by their own kernel.  A stored vector
+    and a product are rounded once each (u of |H v|), each of the projections on the
+    older vectors is of the size of that rounding, and the FP64 sums leave 64 eps."""
+    ed = gpu_ed()
+    phys = wl.kanamori(3, 4, 2.3, 0.4, seed=3)
+    b, H = build(phys, *nn, prec)
+    m, dt, elem = 20, (torch.float64, torch.float32)[prec], (8, 4)[prec]
+    o = ed.options(reorth=reorth, layout=1)
+    ws = torch.zeros(H.tridiag_workspace_bytes(m, o), dtype=torch.uint8, device=DEV)
+    al, be, _ = H.lanczos_tridiag(_v0(b.D, prec, 5), m, o, ws=ws)
+    assert len(al) == m
+    size = (b.D * elem + 255) // 256 * 256
+    ring = 3 if reorth == 0 else m + 1      # the three-term recurrence keeps three vectors
+
+    def vec(i):
+        v = ws[(i % ring) * size:(i % ring) * size + b.D * elem].view(dt)
+        return v, v.double() / v.double().norm()
+
+    unit, y = (2.0 ** -53, 2.0 ** -24)[prec], torch.empty(b.D, dtype=dt, device=DEV)
+    for j in range(m - 1 if reorth == 0 else 1, m):
+        raw, v = vec(j)
+        H.apply(raw.clone(), y)
+        hv = y.double() / raw.double().norm()
+        scale = float(hv.norm())
+        hv -= al[j] * v + be[j - 1] * vec(j - 1)[1]
+        hv -= be[j] * vec(j + 1)[1]
+        bound = (m + 8) * unit * scale + 64 * 2.0 ** -52 * scale
+        assert float(hv.norm()) <= bound, (j, float(hv.norm()), bound)
+        for i in range(j - 1 if reorth == 0 else 0, j + 1):
+            d = float((vec(i)[1] * vec(j + 1)[1]).sum().abs())
+            assert d <= 4 * unit + 64 * 2.0 ** -52 * scale / be[j], (i, j, d)
