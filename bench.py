@@ -413,7 +413,7 @@ def batched_bench():
             ref = np.array([g["sectors"]["%d,%d" % s]["evals"][0] for s in sectors])
     out = {"workload": "kanamori_Ns12_3orb_9bath_all169_sectors", "sum_D": sum_d, "setup_s": round(tset, 3)}
     runs = (("keep8_of_20_reorth3", dict(tol=1e-7, max_basis=20, keep=8, reorth=3, max_iter=3000)),
-            ("basis60_cgs2", dict(tol=1e-7, max_basis=60, reorth=2, max_iter=3000)))
+            ("basis60_reorth2", dict(tol=1e-7, max_basis=60, reorth=2, max_iter=3000)))
     E_main = None
     for key, kw in runs:
         opts = ed.options(**kw)
@@ -641,13 +641,13 @@ def main():
             ns18["fp64"] = apply_leg(4, ed.ED_FP64, max(3, args.steps // 10), 1)
 
     # ---- time to E0, FP32-mixed vs FP64, same start vector and target
-    e0 = e0_cgs2 = None
+    e0 = e0_r2 = None
     if not args.no_e0:
         # implicitly restarted Lanczos keeping 4 of 14 vectors (the fastest setting of
         # a sweep over 10..16 stored vectors keeping 3..8), both projections per read
         e0 = time_to_e0(2, [ed.ED_FP32, ed.ED_FP64], max_basis=14, tol=1e-7, seed_idx=2, reorth=3, keep=4)
         # reference: two full Gram-Schmidt passes, restart from the Ritz vector
-        e0_cgs2 = time_to_e0(2, [ed.ED_FP32, ed.ED_FP64], max_basis=50, tol=1e-7, seed_idx=2, reorth=2)
+        e0_r2 = time_to_e0(2, [ed.ED_FP32, ed.ED_FP64], max_basis=50, tol=1e-7, seed_idx=2, reorth=2)
     e0_16 = None
     if not args.no_e0 and not args.no_ns16:
         # 4x4 periodic Hubbard, U = 4, half filling: E0 and the 4 lowest levels
@@ -699,7 +699,7 @@ def main():
         "hv_ns15_fp64": fp64,
         "hv_ns18": ns18,
         "time_to_e0_ns15": e0,
-        "time_to_e0_ns15_cgs2": e0_cgs2,
+        "time_to_e0_ns15_reorth2": e0_r2,
         "time_to_e0_ns16": e0_16,
         "time_to_e0_ns18": e0_18,
         "batched_ns12": batched,

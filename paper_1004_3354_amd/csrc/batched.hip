@@ -256,7 +256,7 @@ __global__ __launch_bounds__(kBBS) void kb_apply(const BSec<TX, TA> *secs, const
 // outputs and up-spin partners are 16-byte loads.  kb_apply, one column of four
 // rows per item over the CSR tables, needs four to eight times the loads per
 // output: all 169 sectors of the 12-site impurity (1.7e7 elements, FP32), 297 us
-// -> about 125 us per step.  Bound by the latency of its dependent loads: tiles of
+// -> 121 us per step.  Bound by the latency of its dependent loads: tiles of
 // 4096 elements (one work item per thread) beat 2048, 8192 and 16384, and six
 // waves per SIMD (register bound) beat four by 3 % of the whole step.
 template <typename TX>
@@ -775,7 +775,8 @@ __global__ __launch_bounds__(kBBS) void kb_restart_v4(const BSec<TX, TX> *secs, 
 // which every thread then applies to its rows of Q; the coefficients of the kept
 // vectors and the new residual.  If that does not apply (non-finite data, the
 // lowest Ritz value lost) or keep = 0: from the Ritz vector.  Bound by the latency
-// of the rotations' chain, about 40 us for m = 20, keep = 8; the same plans on the
+// of the rotations' chain: 153 us for m = 20, keep = 8 where sectors restart, 4 us where
+// none does (15 us a step over the N_s = 12 batch); the same plans on the
 // host (16 threads, up to a hundred waiting sectors, their states copied there and
 // back) left the GPU idle for 0.1 ms per step on average.  Q in LDS for m <=
 // kPlanLds, else in the sector's Gram matrix, which the restart resets.
@@ -1177,8 +1178,9 @@ static size_t row_tile_lds(const ed_ham_s *h, int nr, size_t elem) {
 }
 static constexpr size_t kRowTileLds = 60 * 1024;
 // Sectors kb_tile takes: down hops packed (or none), the cross table and one group
-// of rows in LDS.  The others (thousands of distinct amplitudes, rows of more than
-// about 3800 FP32 or 1900 FP64 states) go to kb_apply.
+// of rows in LDS.  The others (thousands of distinct amplitudes, more than four
+// cross-term sites, rows of more than about 3800 states: a group is 16 bytes per
+// state in either precision) go to kb_apply.
 static bool row_tile_fits(const ed_ham_s *h, size_t elem) {
     return (h->sp[1].pk_ok || h->sp[1].nnz == 0) && h->koff <= 4 &&
            row_tile_lds(h, (int)std::min<int64_t>(16 / (int64_t)elem, h->dup), elem) <= kRowTileLds;

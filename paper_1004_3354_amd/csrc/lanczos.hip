@@ -15,10 +15,12 @@
 // recurrence, the second time on all of them.  Every other component of Y is at
 // the level of rounding (of the locked vectors' residuals) already before the
 // first projection, which is what a first pass over all vectors would leave,
-// so the second pass ends at the same orthogonality (FP64 1e-15, FP32 1e-8,
-// with explicit and implicit restarts and locked vectors alike) while the
-// stored vectors are read twice per step instead of four times.  W is formed
-// on the fly in FP64 and never stored.
+// so the second pass ends at the same orthogonality while the stored vectors are
+// read twice per step instead of four times.  max |<v_i, v_j>| of the vectors a
+// solve leaves, against two passes over all: FP64 1.0e-15 / 1.0e-15 (D = 4900),
+// 9.0e-15 / 9.2e-15 (D = 853,776, 120 vectors), FP32 6.0e-9 / 6.2e-9, with restarts
+// and vectors locked at 1e-4 FP64 2.4e-15 / 2.4e-15, FP32 4.6e-8 / 4.6e-8.  W is
+// formed on the fly in FP64 and never stored.
 // reorth = 3 gives the same two projections with one read of the basis per
 // step: the second pass's dots are a_i - sum_k G_ik gamma_k with G_ik =
 // <S_i, S_k> (exact for the update Y - sum gamma_k S_k), and the new row of G
@@ -28,7 +30,7 @@
 // All dot products and updates accumulate in FP64 with a fixed reduction
 // order, so runs are bit-reproducible.  The lowest eigenpair of the j x j
 // tridiagonal matrix comes from a one-workgroup multisection (Sturm counts) and
-// inverse iteration; convergence is |beta_j s_j| <= tol max(|theta|, 1).
+// the twisted factorisation; convergence is |beta_j s_j| <= tol max(|theta|, 1).
 #include <algorithm>
 #include <cmath>
 #include <cstdlib>
@@ -723,8 +725,8 @@ __device__ __forceinline__ double wg_reduce(double v, int what, double *sh) {
 //    z_{i+1} = -(beta_i / e_{i+1}) z_i below.  At the lowest eigenvalue T - theta I
 //    is positive semidefinite, so the pivots each side of the twist uses are stable
 //    without pivoting, and the residual is |gamma_r| |z_r| / |z|, rounding level.
-// Bound by the latency of the serial chains: 120 rows 176 -> 58 us, 72 rows 112 ->
-// 39 us (before: the Sturm ratio with a division per row, three inverse iterations
+// Bound by the latency of the serial chains: 120 rows 178 -> 48 us, 72 rows 114 ->
+// 33 us (before: the Sturm ratio with a division per row, three inverse iterations
 // with a pivoted LU by one thread).
 static constexpr int kTriMax = 1024;
 __device__ void k_tridiag_lowest_body(const double *alpha, const double *beta, int m, double *out) {
